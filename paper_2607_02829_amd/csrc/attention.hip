@@ -5,7 +5,7 @@
 // 2D + h*hd); O and dO are [B*S, D]; dqkv mirrors qkv.  lse[b,h,s] is the base-2
 // log-sum-exp of the scaled scores, so P = exp2(s * log2(e)/sqrt(hd) - lse).
 //
-// MFMA kernels (head dim 64 or 128, bf16, v_mfma_f32_32x32x16_bf16).  A workgroup of NW
+// MFMA kernels (head dim 32, 64 or 128, bf16, v_mfma_f32_32x32x16_bf16).  A workgroup of NW
 // waves owns 32 NW rows (32 per wave) of the resident dimension and streams the other one in
 // 64-row tiles of one head:
 //  * forward: a wave owns 32 queries and forms S^T = K Q^T per 32-key unit, so each
@@ -27,7 +27,7 @@
 // dO^T, K^T) are read with ds_read_b64_tr_b16, which hands each lane four consecutive rows
 // of one column, so no transposed copy is ever written.
 //
-// Generic kernels (fp32 storage, or bf16 at head dim 32): one thread per row, online softmax
+// Generic kernels (fp32 storage): one thread per row, online softmax
 // over keys, fp32 throughout.
 #include <type_traits>
 
@@ -48,11 +48,17 @@ constexpr int NSTG = 3;      // LDS stages
 // head dim 64).
 template <int HD>
 constexpr int attn_waves() { return HD == 64 ? 8 : 4; }
+// At head dim 32 the vector work of a score (the exponential, the split of P into two bf16 parts,
+// see split8) outweighs its MFMAs, registers are few, and the small models that use it have few
+// heads: four waves (128 rows) per workgroup, so that more CUs get one.  4050 tokens, four heads:
+// forward 58.7, dK/dV 94.1, dQ 60.0 us, against 4219, 2419 and 2260 us for one thread per row.
+// Waves per SIMD that the register allocation of the templates below leaves room for.
+constexpr int attn_occ(int hd, int nw) { return hd == 64 ? 8 / nw : 2; }
 
 // Geometry of a 64-row tile of one head (head dim HD, bf16).
 template <int HD>
 struct Geo {
-  static_assert(HD == 64 || HD == 128, "MFMA attention head dims");
+  static_assert(HD == 32 || HD == 64 || HD == 128, "MFMA attention head dims");
   static constexpr int AP = HD + 8;     // padded row (bf16) of the output staging tile
   static constexpr int TE = KT * HD;    // bf16 elements of one 64-row tile
   static constexpr int TB = TE * 2;     // bytes of one tile
@@ -80,6 +86,18 @@ SR_DEV bf16x8 neg8(bf16x8 v) {
   return __builtin_bit_cast(bf16x8, w);
 }
 
+// Head dim 32: eight fp32 values as bf16 pairs hi + lo (relative error 2^-18), so that products
+// with bf16 operands on the matrix cores keep what the probabilities and score gradients hold
+// beyond 8 bits: twice the MFMAs of a contraction that is short at this head dim.  Measured
+// against fp64, outputs and gradients are as close as with fp32 probabilities.
+SR_DEV void split8(const float* p, bf16x8& hi, bf16x8& lo) {
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    hi[i] = (__bf16)p[i];
+    lo[i] = (__bf16)(p[i] - (float)hi[i]);
+  }
+}
+
 SR_DEV f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
 
 // 2^x on the hardware unit directly: the softmax arguments are <= 0 (or -inf), where the
@@ -99,6 +117,9 @@ SR_DEV void zero16(f32x16& a) {
 //    a wave's transposed read touches fall in different banks (measured conflict-free for both
 //    read kinds, where plain XOR swizzles within 64-byte groups cost one extra pass per
 //    transposed read).
+//  * HD = 32 (64-byte rows, four to a pass of the banks): rows 4 apart, which share banks, take
+//    different positions, so the fragment reads of 16 consecutive rows cover every bank once; the
+//    four consecutive rows of a half-wave's transposed read are one whole pass by themselves.
 //  * HD = 128 (256-byte rows, each one whole pass of the banks): 16 consecutive rows take 16
 //    different positions (16-byte fragment reads of 16 lanes cover every bank once), and bits
 //    2-3 of the position follow the row mod 4, so the four rows x 64 bytes of a half-wave's
@@ -107,7 +128,8 @@ SR_DEV void zero16(f32x16& a) {
 // constants (instruction offsets rather than address registers).
 template <int HD>
 SR_DEV int swz(int row) {
-  if constexpr (HD == 64) return (((row >> 1) & 1) << 2) | ((row >> 2) & 3);
+  if constexpr (HD == 32) return (row >> 2) & 3;
+  else if constexpr (HD == 64) return (((row >> 1) & 1) << 2) | ((row >> 2) & 3);
   else return ((row & 3) << 2) | ((row >> 2) & 3);
 }
 template <int HD>
@@ -117,10 +139,12 @@ SR_DEV int toff(int row, int chunk) { return row * HD + ((chunk ^ swz<HD>(row)) 
 // into the LDS tile dst: HD / 8 blocks of 1 KB (64 / (HD / 8) rows each); lane l lands at
 // byte 16 l of its block, so it fetches the chunk that the swizzle places there.  Rows past
 // the sample's S tokens are read without a guard: they belong to the next sample (finite
-// values the callers mask) or lie past the tensor, where the buffer load returns zero.
+// values the callers mask) or lie past the tensor, where the buffer load returns zero; at head
+// dim 32 rows at or past `rows` read as zero, so a non-finite neighbouring sample stays out.
 // NW waves share the blocks.
 template <int HD, int NW>
-SR_DEV void tile_load(__amdgpu_buffer_rsrc_t rs, uint32_t base, uint32_t ld, int r0, bf16_t* dst, bool valid = true) {
+SR_DEV void tile_load(__amdgpu_buffer_rsrc_t rs, uint32_t base, uint32_t ld, int r0, int rows, bf16_t* dst,
+                      bool valid = true) {
   using G = Geo<HD>;
   static_assert(G::BLK % NW == 0, "tile blocks per wave");
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
@@ -133,7 +157,7 @@ SR_DEV void tile_load(__amdgpu_buffer_rsrc_t rs, uint32_t base, uint32_t ld, int
     uint32_t off = base + ((uint32_t)(r0 + row) * ld + (uint32_t)c * 8u) * 2u;
     // a load past the last tile keeps the number of loads in flight uniform: it reads beyond
     // every tensor's extent (2 GiB at most), which returns zeros without a memory access
-    if (!valid) off = 0x80000000u;
+    if (!valid || (HD == 32 && r0 + row >= rows)) off = 0x80000000u;
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t*)(dst + blk * 512), 16, off, 0, 0, 0);
   }
 }
@@ -261,7 +285,7 @@ SR_DEV TileId xcd_tile_id() {
 // Queries: Sq rows of q (row stride ldq); keys: Skv rows of kv (row stride ldkv), values D
 // columns after the keys; kv_elems: elements addressable from kv (the buffer's extent).
 template <int HD, int NW>
-__global__ __launch_bounds__(64 * NW, HD == 64 ? 8 / NW : 1) void attn_fwd_mfma(const bf16_t* __restrict__ q, int ldq,
+__global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_fwd_mfma(const bf16_t* __restrict__ q, int ldq,
                                                      const bf16_t* __restrict__ kv, int ldkv, uint32_t kv_elems,
                                                      bf16_t* __restrict__ O, float* __restrict__ lse, int Sq, int Skv,
                                                      int H, int D, float sl2) {
@@ -289,8 +313,8 @@ __global__ __launch_bounds__(64 * NW, HD == 64 ? 8 / NW : 1) void attn_fwd_mfma(
 
   constexpr int kLoads = 2 * (G::BLK / NW);   // buffer loads per thread per tile (two tiles)
   auto load = [&](int t, int s) {
-    tile_load<HD, NW>(rq, kbase, (uint32_t)ldkv, t * KT, smem + s * 2 * TE, t < nt);
-    tile_load<HD, NW>(rq, vbase, (uint32_t)ldkv, t * KT, smem + s * 2 * TE + TE, t < nt);
+    tile_load<HD, NW>(rq, kbase, (uint32_t)ldkv, t * KT, Skv, smem + s * 2 * TE, t < nt);
+    tile_load<HD, NW>(rq, vbase, (uint32_t)ldkv, t * KT, Skv, smem + s * 2 * TE + TE, t < nt);
   };
   auto mask = [&](f32x16& sc, int k0) {   // keys past Skv do not exist
 #pragma unroll
@@ -357,11 +381,27 @@ __global__ __launch_bounds__(64 * NW, HD == 64 ? 8 / NW : 1) void attn_fwd_mfma(
       m_run = m_ref;
     }
     const float nm = -m_run * sl2;
-    bf16x8 pb0[2], pb1[2];
+    bf16x8 pb0[2], pb1[2], pl0[2], pl1[2];   // pl: low parts at head dim 32
+    if constexpr (HD == 32) {
+      float p0[16], p1[16];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      pb0[r >> 3][r & 7] = (__bf16)ex2(fmaf(sc0[r], sl2, nm));
-      pb1[r >> 3][r & 7] = (__bf16)ex2(fmaf(sc1[r], sl2, nm));
+      for (int r = 0; r < 16; ++r) {
+        p0[r] = ex2(fmaf(sc0[r], sl2, nm));
+        p1[r] = ex2(fmaf(sc1[r], sl2, nm));
+      }
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+        split8(p0 + 8 * kk, pb0[kk], pl0[kk]);
+        split8(p1 + 8 * kk, pb1[kk], pl1[kk]);
+        lsum = mfma(ones, pl0[kk], lsum);
+        lsum = mfma(ones, pl1[kk], lsum);
+      }
+    } else {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        pb0[r >> 3][r & 7] = (__bf16)ex2(fmaf(sc0[r], sl2, nm));
+        pb1[r >> 3][r & 7] = (__bf16)ex2(fmaf(sc1[r], sl2, nm));
+      }
     }
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk) {
@@ -373,8 +413,13 @@ __global__ __launch_bounds__(64 * NW, HD == 64 ? 8 / NW : 1) void attn_fwd_mfma(
     for (int db = 0; db < DB; ++db)
 #pragma unroll
       for (int kk = 0; kk < 2; ++kk) {
-        o[db] = mfma(vt0[db][kk].settle(), pb0[kk], o[db]);
-        o[db] = mfma(vt1[db][kk].settle(), pb1[kk], o[db]);
+        const bf16x8 v0 = vt0[db][kk].settle(), v1 = vt1[db][kk].settle();
+        o[db] = mfma(v0, pb0[kk], o[db]);
+        o[db] = mfma(v1, pb1[kk], o[db]);
+        if constexpr (HD == 32) {
+          o[db] = mfma(v0, pl0[kk], o[db]);
+          o[db] = mfma(v1, pl1[kk], o[db]);
+        }
       }
   };
 
@@ -428,7 +473,7 @@ __global__ __launch_bounds__(64 * NW, HD == 64 ? 8 / NW : 1) void attn_fwd_mfma(
 template <int HD, int NW>
 // Keys: Skv rows of kv (stride ldkv, values D columns on); queries: Sq rows of q (stride ldq,
 // q_elems addressable elements); dK to dk_out (stride ldo), dV D columns after it.
-__global__ __launch_bounds__(64 * NW, HD == 64 ? 8 / NW : 1) void attn_bwd_dkv_mfma(const bf16_t* __restrict__ q, int ldq,
+__global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_bwd_dkv_mfma(const bf16_t* __restrict__ q, int ldq,
                                                          uint32_t q_elems, const bf16_t* __restrict__ kv, int ldkv,
                                                          const bf16_t* __restrict__ dO,
                                                          const float* __restrict__ lse, const float* __restrict__ delta,
@@ -467,8 +512,8 @@ __global__ __launch_bounds__(64 * NW, HD == 64 ? 8 / NW : 1) void attn_bwd_dkv_m
   const uint32_t dbase = (uint32_t)(((size_t)b * Sq * D + hh * HD) * 2);
   const uint32_t lbase = (uint32_t)(((size_t)b * H + hh) * Sq * 4);
   auto load = [&](int t, int s) {
-    tile_load<HD, NW>(rq, qbase, (uint32_t)ldq, t * KT, smem + s * 2 * TE);
-    tile_load<HD, NW>(rd, dbase, (uint32_t)D, t * KT, smem + s * 2 * TE + TE);
+    tile_load<HD, NW>(rq, qbase, (uint32_t)ldq, t * KT, Sq, smem + s * 2 * TE);
+    tile_load<HD, NW>(rd, dbase, (uint32_t)D, t * KT, Sq, smem + s * 2 * TE + TE);
     const uint32_t lo = lbase + (uint32_t)(t * KT + lane) * 4u;
     if (wid == 0) __builtin_amdgcn_raw_ptr_buffer_load_lds(rl, (lds_ptr_t*)(fsm + s * 2 * KT), 4, lo, 0, 0, 0);
     if (wid == 1) __builtin_amdgcn_raw_ptr_buffer_load_lds(rdl, (lds_ptr_t*)(fsm + s * 2 * KT + KT), 4, lo, 0, 0, 0);
@@ -498,7 +543,8 @@ __global__ __launch_bounds__(64 * NW, HD == 64 ? 8 / NW : 1) void attn_bwd_dkv_m
     f32x16 dpv;
     dp_of(s, u, dpv);
     const float* ls = fsm + s * 2 * KT + u * 32;
-    bf16x8 pb[2], sb[2];
+    bf16x8 pb[2], sb[2], pl[2], sl[2];   // pl, sl: low parts at head dim 32
+    float pf[HD == 32 ? 16 : 1], sf[HD == 32 ? 16 : 1];
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int ql = srow(r, h32);
@@ -507,8 +553,20 @@ __global__ __launch_bounds__(64 * NW, HD == 64 ? 8 / NW : 1) void attn_bwd_dkv_m
       if constexpr (decltype(rag)::value) {
         if (q0 + ql >= Sq) { p = 0.f; ds = 0.f; }
       }
-      pb[r >> 3][r & 7] = (__bf16)p;
-      sb[r >> 3][r & 7] = (__bf16)ds;
+      if constexpr (HD == 32) {
+        pf[r] = p;
+        sf[r] = ds;
+      } else {
+        pb[r >> 3][r & 7] = (__bf16)p;
+        sb[r >> 3][r & 7] = (__bf16)ds;
+      }
+    }
+    if constexpr (HD == 32) {
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+        split8(pf + 8 * kk, pb[kk], pl[kk]);
+        split8(sf + 8 * kk, sb[kk], sl[kk]);
+      }
     }
     // keep the transposed fragment reads after the arithmetic: hoisted above it they hold
     // registers through the exp2 chain (measured slower)
@@ -519,8 +577,14 @@ __global__ __launch_bounds__(64 * NW, HD == 64 ? 8 / NW : 1) void attn_bwd_dkv_m
     for (int db = 0; db < DB; ++db)
 #pragma unroll
       for (int kk = 0; kk < 2; ++kk) {
-        dv[db] = mfma(tr_frag<HD>(dOs, u * 32 + kk * 16, db * 32), pb[kk], dv[db]);
-        dk[db] = mfma(tr_frag<HD>(Qs, u * 32 + kk * 16, db * 32), sb[kk], dk[db]);
+        const bf16x8 dof = tr_frag<HD>(dOs, u * 32 + kk * 16, db * 32);
+        dv[db] = mfma(dof, pb[kk], dv[db]);
+        const bf16x8 qfr = tr_frag<HD>(Qs, u * 32 + kk * 16, db * 32);
+        dk[db] = mfma(qfr, sb[kk], dk[db]);
+        if constexpr (HD == 32) {
+          dv[db] = mfma(dof, pl[kk], dv[db]);
+          dk[db] = mfma(qfr, sl[kk], dk[db]);
+        }
       }
   };
 
@@ -532,7 +596,7 @@ __global__ __launch_bounds__(64 * NW, HD == 64 ? 8 / NW : 1) void attn_bwd_dkv_m
     constexpr int s0 = decltype(stg)::value, s2 = (s0 + 2) % NSTG;
     const bool rag = ragged && t + 1 == nt;
     // head dim 128: one query unit at a time (unrolled, the two units' live ranges spill)
-#pragma unroll (HD == 64 ? 2 : 1)
+#pragma unroll (HD <= 64 ? 2 : 1)
     for (int u = 0; u < 2; ++u) {
       f32x16 sv;
       s_of(s0, u, sv);
@@ -701,8 +765,8 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_h128(const bf16_t* __rest
   // that every wave has LPT loads per tile in flight
   auto fill = [&](int t, int s) __attribute__((always_inline)) {
     const bool valid = t < nt;
-    tile_load<HD, NW>(rq, qbase, (uint32_t)ldq, t * KT, smem + s * TE, valid);
-    tile_load<HD, NW>(rd, dbase, (uint32_t)D, t * KT, smem + NST * TE + s * TE, valid);
+    tile_load<HD, NW>(rq, qbase, (uint32_t)ldq, t * KT, Sq, smem + s * TE, valid);
+    tile_load<HD, NW>(rd, dbase, (uint32_t)D, t * KT, Sq, smem + NST * TE + s * TE, valid);
     const uint32_t lo = valid ? lbase + (uint32_t)(t * KT + lane) * 4u : 0x80000000u;
     if (wid == 0) __builtin_amdgcn_raw_ptr_buffer_load_lds(rl, (lds_ptr_t*)(fsm + s * 2 * KT), 4, lo, 0, 0, 0);
     else if (wid == 1) __builtin_amdgcn_raw_ptr_buffer_load_lds(rdl, (lds_ptr_t*)(fsm + s * 2 * KT + KT), 4, lo, 0, 0, 0);
@@ -952,7 +1016,7 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_h128(const bf16_t* __rest
 template <int HD, int NW>
 // Queries: Sq rows of q (stride ldq); keys: Skv rows of kv (stride ldkv, kv_elems addressable
 // elements, values D columns on); dQ to dq_out (stride ldo).
-__global__ __launch_bounds__(64 * NW, HD == 64 ? 8 / NW : 1) void attn_bwd_dq_mfma(const bf16_t* __restrict__ q, int ldq,
+__global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_bwd_dq_mfma(const bf16_t* __restrict__ q, int ldq,
                                                         const bf16_t* __restrict__ kv, int ldkv, uint32_t kv_elems,
                                                         const bf16_t* __restrict__ dO,
                                                         const float* __restrict__ lse, const float* __restrict__ delta,
@@ -996,8 +1060,8 @@ __global__ __launch_bounds__(64 * NW, HD == 64 ? 8 / NW : 1) void attn_bwd_dq_mf
   ta.init(lds_addr(smem), lane);
   constexpr int kLoads = 2 * (G::BLK / NW);   // buffer loads per thread per tile (two tiles)
   auto load = [&](int t, int s) {
-    tile_load<HD, NW>(rq, kbase, (uint32_t)ldkv, t * KT, smem + s * 2 * TE, t < nt);
-    tile_load<HD, NW>(rq, vbase, (uint32_t)ldkv, t * KT, smem + s * 2 * TE + TE, t < nt);
+    tile_load<HD, NW>(rq, kbase, (uint32_t)ldkv, t * KT, Skv, smem + s * 2 * TE, t < nt);
+    tile_load<HD, NW>(rq, vbase, (uint32_t)ldkv, t * KT, Skv, smem + s * 2 * TE + TE, t < nt);
   };
   // K (tile 0) or V (tile 1) row fragments of key unit U of stage SG
   auto read_rows = [&](auto sg, auto uu, auto tl, RawFrag<true> (&fr)[KS]) {
@@ -1024,7 +1088,8 @@ __global__ __launch_bounds__(64 * NW, HD == 64 ? 8 / NW : 1) void attn_bwd_dq_mf
         ta.template read<SG * SGB, U * 32 + decltype(kk)::value * 16, decltype(db)::value>(fk[db.value][kk.value]);
       });
     });
-    bf16x8 sb[2];
+    bf16x8 sb[2], sl[2];   // sl: low parts at head dim 32
+    float sf[HD == 32 ? 16 : 1];
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const float p = ex2(fmaf(sv[r], sl2, nlse));
@@ -1032,13 +1097,22 @@ __global__ __launch_bounds__(64 * NW, HD == 64 ? 8 / NW : 1) void attn_bwd_dq_mf
       if constexpr (decltype(rag)::value) {
         if (k0 + srow(r, h32) >= Skv) ds = 0.f;
       }
-      sb[r >> 3][r & 7] = (__bf16)ds;
+      if constexpr (HD == 32) sf[r] = ds;
+      else sb[r >> 3][r & 7] = (__bf16)ds;
+    }
+    if constexpr (HD == 32) {
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) split8(sf + 8 * kk, sb[kk], sl[kk]);
     }
     lgkm_wait<0>();
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
-      for (int kk = 0; kk < 2; ++kk) dq[db] = mfma(fk[db][kk].settle(), sb[kk], dq[db]);
+      for (int kk = 0; kk < 2; ++kk) {
+        const bf16x8 kt = fk[db][kk].settle();
+        dq[db] = mfma(kt, sb[kk], dq[db]);
+        if constexpr (HD == 32) dq[db] = mfma(kt, sl[kk], dq[db]);
+      }
   };
 
   load(0, 0);
@@ -1170,8 +1244,8 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dq_h128(const bf16_t* __restr
   const uint32_t vbase = kbase + (uint32_t)D * 2u;
   auto fill = [&](int t, int s) __attribute__((always_inline)) {
     const bool valid = t < nt;
-    tile_load<HD, NW>(rkv, kbase, (uint32_t)ldkv, t * KT, smem + s * TE, valid);
-    tile_load<HD, NW>(rkv, vbase, (uint32_t)ldkv, t * KT, smem + NST * TE + s * TE, valid);
+    tile_load<HD, NW>(rkv, kbase, (uint32_t)ldkv, t * KT, Skv, smem + s * TE, valid);
+    tile_load<HD, NW>(rkv, vbase, (uint32_t)ldkv, t * KT, Skv, smem + NST * TE + s * TE, valid);
   };
 
   const uint32_t sbase = lds_addr(smem);
@@ -1431,8 +1505,8 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_h128(const bf16_t* __restrict
   const uint32_t vbase = kbase + (uint32_t)D * 2u;
   auto fill = [&](int t, int s) __attribute__((always_inline)) {
     const bool valid = t < nt;
-    tile_load<HD, NW>(rkv, kbase, (uint32_t)ldkv, t * KT, smem + s * TE, valid);
-    tile_load<HD, NW>(rkv, vbase, (uint32_t)ldkv, t * KT, smem + NST * TE + s * TE, valid);
+    tile_load<HD, NW>(rkv, kbase, (uint32_t)ldkv, t * KT, Skv, smem + s * TE, valid);
+    tile_load<HD, NW>(rkv, vbase, (uint32_t)ldkv, t * KT, Skv, smem + NST * TE + s * TE, valid);
   };
   const uint32_t sbase = lds_addr(smem);
   uint32_t ra[KS];
@@ -1799,7 +1873,7 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_colsum_mfma(const bf16_t
   const uint32_t qbase = (uint32_t)(((size_t)b * S * ld + hh * HD) * 2);
   const uint32_t lbase = (uint32_t)(((size_t)b * H + hh) * S * 4);
   auto load = [&](int t, int s) {
-    tile_load<HD, NW>(rq, qbase, (uint32_t)ld, t * KT, smem + s * TE);
+    tile_load<HD, NW>(rq, qbase, (uint32_t)ld, t * KT, S, smem + s * TE);
     const uint32_t lo = lbase + (uint32_t)(t * KT + lane) * 4u;
     if (wid == 0) __builtin_amdgcn_raw_ptr_buffer_load_lds(rl, (lds_ptr_t*)(fsm + s * KT), 4, lo, 0, 0, 0);
   };
@@ -1879,7 +1953,7 @@ __global__ __launch_bounds__(64) void attn_colsum_simple(const Ta* __restrict__ 
 
 static inline float attn_sl2(int hd) { return 1.4426950408889634f / sqrtf((float)hd); }
 
-bool attn_uses_mfma(int dtype, int hd) { return dtype == kBF16 && (hd == 64 || hd == 128); }
+bool attn_uses_mfma(int dtype, int hd) { return dtype == kBF16 && (hd == 32 || hd == 64 || hd == 128); }
 
 template <typename Ta>
 static hipError_t fwd_simple(const Ta* qkv, Ta* O, float* lse, int B, int S, int H, int D, int hd, hipStream_t st) {
@@ -1929,6 +2003,7 @@ static hipError_t fwd_mfma_hd(const bf16_t* q, int ldq, const bf16_t* kv, int ld
 hipError_t launch_attn_fwd_mfma(const bf16_t* q, int ldq, const bf16_t* kv, int ldkv, uint32_t kv_elems, bf16_t* O,
                                 float* lse, int B, int Sq, int Skv, int H, int D, hipStream_t st) {
   if (D / H == 128) return fwd_mfma_hd<128>(q, ldq, kv, ldkv, kv_elems, O, lse, B, Sq, Skv, H, D, st);
+  if (D / H == 32) return fwd_mfma_hd<32>(q, ldq, kv, ldkv, kv_elems, O, lse, B, Sq, Skv, H, D, st);
   return fwd_mfma_hd<64>(q, ldq, kv, ldkv, kv_elems, O, lse, B, Sq, Skv, H, D, st);
 }
 
@@ -1952,6 +2027,7 @@ hipError_t launch_attn_dkv_mfma(const bf16_t* q, int ldq, uint32_t q_elems, cons
                                 int Sq, int Skv, int H, int D, hipStream_t st) {
   if (D / H == 128)
     return dkv_mfma_hd<128>(q, ldq, q_elems, kv, ldkv, dO, lse, delta, dk_out, ldo, B, Sq, Skv, H, D, st);
+  if (D / H == 32) return dkv_mfma_hd<32>(q, ldq, q_elems, kv, ldkv, dO, lse, delta, dk_out, ldo, B, Sq, Skv, H, D, st);
   return dkv_mfma_hd<64>(q, ldq, q_elems, kv, ldkv, dO, lse, delta, dk_out, ldo, B, Sq, Skv, H, D, st);
 }
 
@@ -1975,6 +2051,7 @@ hipError_t launch_attn_dq_mfma(const bf16_t* q, int ldq, const bf16_t* kv, int l
                                int Sq, int Skv, int H, int D, hipStream_t st) {
   if (D / H == 128)
     return dq_mfma_hd<128>(q, ldq, kv, ldkv, kv_elems, dO, lse, delta, dq_out, ldo, B, Sq, Skv, H, D, st);
+  if (D / H == 32) return dq_mfma_hd<32>(q, ldq, kv, ldkv, kv_elems, dO, lse, delta, dq_out, ldo, B, Sq, Skv, H, D, st);
   return dq_mfma_hd<64>(q, ldq, kv, ldkv, kv_elems, dO, lse, delta, dq_out, ldo, B, Sq, Skv, H, D, st);
 }
 
@@ -1986,7 +2063,6 @@ hipError_t launch_attn_fwd(int dtype, const void* qkv, void* O, float* lse, int 
     return launch_attn_fwd_mfma(q, 3 * D, q + D, 3 * D, (uint32_t)((size_t)B * S * 3 * D - D), (bf16_t*)O, lse, B,
                                 S, S, H, D, st);
   }
-  if (dtype == kBF16) return fwd_simple((const bf16_t*)qkv, (bf16_t*)O, lse, B, S, H, D, hd, st);
   return fwd_simple((const float*)qkv, (float*)O, lse, B, S, H, D, hd, st);
 }
 
@@ -2013,8 +2089,6 @@ hipError_t launch_attn_bwd(int dtype, const void* qkv, const void* dO, const flo
     return hipSuccess;
   }
   ProfScope ps("attn_bwd_generic", 8.0 * B * (double)S * S * D, 0, st);
-  if (dtype == kBF16)
-    return bwd_simple((const bf16_t*)qkv, (const bf16_t*)dO, lse, delta, (bf16_t*)dqkv, B, S, H, D, hd, st);
   return bwd_simple((const float*)qkv, (const float*)dO, lse, delta, (float*)dqkv, B, S, H, D, hd, st);
 }
 

@@ -164,7 +164,6 @@ hipError_t launch_xattn_fwd(int dtype, const void* q, const void* kv, void* O, f
   if (attn_uses_mfma(dtype, D / H))
     return launch_attn_fwd_mfma((const bf16_t*)q, D, (const bf16_t*)kv, 2 * D, (uint32_t)((size_t)B * Skv * 2 * D),
                                 (bf16_t*)O, lse, B, Sq, Skv, H, D, st);
-  if (dtype == kBF16) return xfwd((const bf16_t*)q, (const bf16_t*)kv, (bf16_t*)O, lse, B, Sq, Skv, H, D, st);
   return xfwd((const float*)q, (const float*)kv, (float*)O, lse, B, Sq, Skv, H, D, st);
 }
 
@@ -180,9 +179,6 @@ hipError_t launch_xattn_bwd(int dtype, const void* q, const void* kv, const void
     return launch_attn_dq_mfma(qb, D, kvb, 2 * D, (uint32_t)((size_t)B * Skv * 2 * D), dOb, lse, delta, (bf16_t*)dq, D,
                                B, Sq, Skv, H, D, st);
   }
-  if (dtype == kBF16)
-    return xbwd((const bf16_t*)q, (const bf16_t*)kv, (const bf16_t*)dO, lse, delta, (bf16_t*)dq, (bf16_t*)dkv, B, Sq,
-                Skv, H, D, st);
   return xbwd((const float*)q, (const float*)kv, (const float*)dO, lse, delta, (float*)dq, (float*)dkv, B, Sq, Skv, H,
               D, st);
 }
