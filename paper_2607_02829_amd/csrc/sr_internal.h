@@ -146,6 +146,10 @@ hipError_t launch_attn_delta(int dtype, const void* dO, const void* O, int B, in
                              hipStream_t st);
 
 hipError_t launch_gemm(const GemmDesc& g, int epi, const EpiArgs& ep, hipStream_t st);
+// fp32 GEMMs of the block on the fp32 matrix instructions (gemm_f32.hip): whether this product is
+// one of them, and its launch.
+bool gemm_f32_takes(const GemmDesc& g, int epi);
+hipError_t launch_gemm_f32(const GemmDesc& g, int epi, const EpiArgs& ep, hipStream_t st);
 // Weight gradient dW[M x N] = sum_k A(m, k) B(n, k) over tokens k (both operands token-major)
 // and db[m] = sum_k A(m, k) (optional).  part / dbpart: scratch of the sizes below.
 // A weight gradient's reduction of its split-K planes (part: splits planes of n) into out and of
