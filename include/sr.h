@@ -45,7 +45,7 @@
  *    F MLP width, n_blocks middle blocks; S = K (routed) or L (dense) tokens per
  *    sample inside the stack.
  *  - Support: D % 64 == 0, F % 64 == 0, D <= 2048, head dim D/H in {32, 64, 128}
- *    (bf16 runs the MFMA attention kernels, fp32 storage a generic fp32-accumulating kernel); 1 <= K <= L; B*L*D*elt < 2^31 bytes per
+ *    (bf16 and fp32 storage each run matrix-core attention kernels with fp32 accumulation); 1 <= K <= L; B*L*D*elt < 2^31 bytes per
  *    token tensor, and for the block-stack calls also B*S*max(F, 3D)*4 < 2^31 with S the
  *    call's rows per sample (the S or K routed tokens; L for the dense calls), which size the
  *    internal fp32 buffers.  Anything else returns SR_EUNSUPPORTED.
@@ -250,8 +250,7 @@ SR_API sr_status sr_routed_blocks_bwd(const sr_config* cfg, int32_t K, const int
  * {32, 64, 128}); L, F, n_blocks, kind, ln_eps and idx_shared are ignored.
  *   q: [B,Sq,D]; kv: [B,Skv,2D] (k of head h at columns h*hd .., v at D + h*hd ..);
  *   O: [B,Sq,D] out; lse: [B,H,Sq] fp32 out, the base-2 log-sum-exp of the scaled scores.
- * bf16 runs the MFMA attention kernels (the self-attention kernels, given the two buffers and
- * token counts); fp32 generic kernels.  Deterministic. */
+ * Runs the self-attention kernels, given the two buffers and token counts.  Deterministic. */
 SR_API sr_status sr_cross_attention_fwd(const sr_config* cfg, int32_t Sq, int32_t Skv, const void* q,
                                  const void* kv, void* O, float* lse, void* stream);
 

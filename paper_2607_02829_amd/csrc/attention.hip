@@ -27,8 +27,8 @@
 // dO^T, K^T) are read with ds_read_b64_tr_b16, which hands each lane four consecutive rows
 // of one column, so no transposed copy is ever written.
 //
-// Generic kernels (fp32 storage): one thread per row, online softmax
-// over keys, fp32 throughout.
+// The fp32 storage mode's kernels are in attention_f32.hip; the column sums of fp32 storage and of
+// head dims 32 and 128 are a generic kernel (one thread per key, fp32).
 #include <type_traits>
 
 #include "common.h"
@@ -1727,119 +1727,6 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_h128(const bf16_t* __restrict
   unstage<HD, NW>(smem, O + (size_t)b * Sq * D + hh * HD, D, id.blk * (32 * NW), Sq);
 }
 
-// ------------------------------------------------------------------------------ generic kernels
-
-template <typename Ta, int HDT>
-__global__ __launch_bounds__(64) void attn_fwd_simple(const Ta* __restrict__ qkv, Ta* __restrict__ O,
-                                                      float* __restrict__ lse, int S, int H, int D, float sl2) {
-  const int b = blockIdx.z, hh = blockIdx.y;
-  const int q = blockIdx.x * 64 + threadIdx.x;
-  if (q >= S) return;
-  const size_t ld = 3 * (size_t)D;
-  const Ta* base = qkv + (size_t)b * S * ld;
-  float qv[HDT], acc[HDT];
-#pragma unroll
-  for (int d = 0; d < HDT; ++d) { qv[d] = to_f32<Ta>(base[(size_t)q * ld + hh * HDT + d]); acc[d] = 0.f; }
-  float m = -INFINITY, l = 0.f;
-  for (int k = 0; k < S; ++k) {
-    const Ta* kr = base + (size_t)k * ld + D + hh * HDT;
-    const Ta* vr = base + (size_t)k * ld + 2 * D + hh * HDT;
-    float s = 0.f;
-#pragma unroll
-    for (int d = 0; d < HDT; ++d) s = fmaf(qv[d], to_f32<Ta>(kr[d]), s);
-    s *= sl2;
-    const float mn = fmaxf(m, s);
-    const float a = exp2f(m - mn), p = exp2f(s - mn);
-    l = l * a + p;
-#pragma unroll
-    for (int d = 0; d < HDT; ++d) acc[d] = acc[d] * a + p * to_f32<Ta>(vr[d]);
-    m = mn;
-  }
-  Ta* orow = O + ((size_t)b * S + q) * D + hh * HDT;
-#pragma unroll
-  for (int d = 0; d < HDT; ++d) orow[d] = from_f32<Ta>(acc[d] / l);
-  lse[((size_t)b * H + hh) * S + q] = m + log2f(l);
-}
-
-template <typename Ta, int HDT>
-__global__ __launch_bounds__(64) void attn_bwd_dq_simple(const Ta* __restrict__ qkv, const Ta* __restrict__ dO,
-                                                         const float* __restrict__ lse, const float* __restrict__ delta,
-                                                         Ta* __restrict__ dqkv, int S, int H, int D, float sl2,
-                                                         float scale) {
-  const int b = blockIdx.z, hh = blockIdx.y;
-  const int q = blockIdx.x * 64 + threadIdx.x;
-  if (q >= S) return;
-  const size_t ld = 3 * (size_t)D;
-  const Ta* base = qkv + (size_t)b * S * ld;
-  float qv[HDT], dov[HDT], acc[HDT];
-#pragma unroll
-  for (int d = 0; d < HDT; ++d) {
-    qv[d] = to_f32<Ta>(base[(size_t)q * ld + hh * HDT + d]);
-    dov[d] = to_f32<Ta>(dO[((size_t)b * S + q) * D + hh * HDT + d]);
-    acc[d] = 0.f;
-  }
-  const float L2 = lse[((size_t)b * H + hh) * S + q], dl = delta[((size_t)b * H + hh) * S + q];
-  for (int k = 0; k < S; ++k) {
-    const Ta* kr = base + (size_t)k * ld + D + hh * HDT;
-    const Ta* vr = base + (size_t)k * ld + 2 * D + hh * HDT;
-    float s = 0.f, dp = 0.f;
-#pragma unroll
-    for (int d = 0; d < HDT; ++d) {
-      s = fmaf(qv[d], to_f32<Ta>(kr[d]), s);
-      dp = fmaf(dov[d], to_f32<Ta>(vr[d]), dp);
-    }
-    const float p = exp2f(s * sl2 - L2);
-    const float ds = p * (dp - dl);
-#pragma unroll
-    for (int d = 0; d < HDT; ++d) acc[d] = fmaf(ds, to_f32<Ta>(kr[d]), acc[d]);
-  }
-  Ta* out = dqkv + ((size_t)b * S + q) * ld + hh * HDT;
-#pragma unroll
-  for (int d = 0; d < HDT; ++d) out[d] = from_f32<Ta>(acc[d] * scale);
-}
-
-template <typename Ta, int HDT>
-__global__ __launch_bounds__(64) void attn_bwd_dkv_simple(const Ta* __restrict__ qkv, const Ta* __restrict__ dO,
-                                                          const float* __restrict__ lse, const float* __restrict__ delta,
-                                                          Ta* __restrict__ dqkv, int S, int H, int D, float sl2,
-                                                          float scale) {
-  const int b = blockIdx.z, hh = blockIdx.y;
-  const int k = blockIdx.x * 64 + threadIdx.x;
-  if (k >= S) return;
-  const size_t ld = 3 * (size_t)D;
-  const Ta* base = qkv + (size_t)b * S * ld;
-  float kv[HDT], vv[HDT], dk[HDT], dv[HDT];
-#pragma unroll
-  for (int d = 0; d < HDT; ++d) {
-    kv[d] = to_f32<Ta>(base[(size_t)k * ld + D + hh * HDT + d]);
-    vv[d] = to_f32<Ta>(base[(size_t)k * ld + 2 * D + hh * HDT + d]);
-    dk[d] = 0.f; dv[d] = 0.f;
-  }
-  for (int q = 0; q < S; ++q) {
-    const Ta* qr = base + (size_t)q * ld + hh * HDT;
-    const Ta* dr = dO + ((size_t)b * S + q) * D + hh * HDT;
-    float s = 0.f, dp = 0.f;
-#pragma unroll
-    for (int d = 0; d < HDT; ++d) {
-      s = fmaf(to_f32<Ta>(qr[d]), kv[d], s);
-      dp = fmaf(to_f32<Ta>(dr[d]), vv[d], dp);
-    }
-    const float p = exp2f(s * sl2 - lse[((size_t)b * H + hh) * S + q]);
-    const float ds = p * (dp - delta[((size_t)b * H + hh) * S + q]);
-#pragma unroll
-    for (int d = 0; d < HDT; ++d) {
-      dv[d] = fmaf(p, to_f32<Ta>(dr[d]), dv[d]);
-      dk[d] = fmaf(ds, to_f32<Ta>(qr[d]), dk[d]);
-    }
-  }
-  Ta* out = dqkv + ((size_t)b * S + k) * ld + hh * HDT;
-#pragma unroll
-  for (int d = 0; d < HDT; ++d) {
-    out[D + d] = from_f32<Ta>(dk[d] * scale);
-    out[2 * D + d] = from_f32<Ta>(dv[d]);
-  }
-}
-
 // ------------------------------------------------------------------------- column sums
 // colsum[b,h,j] = sum over the S queries i of P[i,j], P = exp2(s * sl2 - lse) the forward's
 // probabilities: the attention token j receives in head h.  MFMA: the dK/dV kernel's score
@@ -1955,29 +1842,6 @@ static inline float attn_sl2(int hd) { return 1.4426950408889634f / sqrtf((float
 
 bool attn_uses_mfma(int dtype, int hd) { return dtype == kBF16 && (hd == 32 || hd == 64 || hd == 128); }
 
-template <typename Ta>
-static hipError_t fwd_simple(const Ta* qkv, Ta* O, float* lse, int B, int S, int H, int D, int hd, hipStream_t st) {
-  dim3 g((S + 63) / 64, H, B);
-  const float sl2 = attn_sl2(hd);
-  if (hd == 32) SR_LAUNCH((attn_fwd_simple<Ta, 32>), g, dim3(64), 0, st, qkv, O, lse, S, H, D, sl2);
-  else if (hd == 64) SR_LAUNCH((attn_fwd_simple<Ta, 64>), g, dim3(64), 0, st, qkv, O, lse, S, H, D, sl2);
-  else SR_LAUNCH((attn_fwd_simple<Ta, 128>), g, dim3(64), 0, st, qkv, O, lse, S, H, D, sl2);
-  return hipGetLastError();
-}
-
-template <typename Ta>
-static hipError_t bwd_simple(const Ta* qkv, const Ta* dO, const float* lse, const float* delta, Ta* dqkv, int B,
-                             int S, int H, int D, int hd, hipStream_t st) {
-  dim3 g((S + 63) / 64, H, B);
-  const float sl2 = attn_sl2(hd), sc = 1.0f / sqrtf((float)hd);
-#define SR_ABS(HDV)                                                                                              \
-  SR_LAUNCH((attn_bwd_dq_simple<Ta, HDV>), g, dim3(64), 0, st, qkv, dO, lse, delta, dqkv, S, H, D, sl2, sc); \
-  SR_LAUNCH((attn_bwd_dkv_simple<Ta, HDV>), g, dim3(64), 0, st, qkv, dO, lse, delta, dqkv, S, H, D, sl2, sc)
-  if (hd == 32) { SR_ABS(32); } else if (hd == 64) { SR_ABS(64); } else { SR_ABS(128); }
-#undef SR_ABS
-  return hipGetLastError();
-}
-
 #define SR_TRY_HIP(x)                 \
   do {                                \
     hipError_t e_ = (x);              \
@@ -2063,7 +1927,9 @@ hipError_t launch_attn_fwd(int dtype, const void* qkv, void* O, float* lse, int 
     return launch_attn_fwd_mfma(q, 3 * D, q + D, 3 * D, (uint32_t)((size_t)B * S * 3 * D - D), (bf16_t*)O, lse, B,
                                 S, S, H, D, st);
   }
-  return fwd_simple((const float*)qkv, (float*)O, lse, B, S, H, D, hd, st);
+  const float* q = (const float*)qkv;
+  const uint32_t all = (uint32_t)((size_t)B * S * 3 * D);
+  return launch_attn_fwd_f32(q, 3 * D, all, q + D, 3 * D, all - D, (float*)O, lse, B, S, S, H, D, st);
 }
 
 hipError_t launch_attn_bwd(int dtype, const void* qkv, const void* dO, const float* lse, const float* delta,
@@ -2089,7 +1955,10 @@ hipError_t launch_attn_bwd(int dtype, const void* qkv, const void* dO, const flo
     return hipSuccess;
   }
   ProfScope ps("attn_bwd_generic", 8.0 * B * (double)S * S * D, 0, st);
-  return bwd_simple((const float*)qkv, (const float*)dO, lse, delta, (float*)dqkv, B, S, H, D, hd, st);
+  const float* q = (const float*)qkv;
+  const uint32_t all = (uint32_t)((size_t)B * S * 3 * D);
+  return launch_attn_bwd_f32(q, 3 * D, all, q + D, 3 * D, all - D, (const float*)dO, lse, delta, (float*)dqkv, 3 * D,
+                             (float*)dqkv + D, 3 * D, B, S, S, H, D, st);
 }
 
 template <typename Ta>

@@ -193,6 +193,12 @@ hipError_t launch_attn_dkv_mfma(const uint16_t* q, int ldq, uint32_t q_elems, co
 hipError_t launch_attn_dq_mfma(const uint16_t* q, int ldq, const uint16_t* kv, int ldkv, uint32_t kv_elems,
                                const uint16_t* dO, const float* lse, const float* delta, uint16_t* dq_out, int ldo, int B,
                                int Sq, int Skv, int H, int D, hipStream_t st);
+// fp32 storage (attention_f32.hip): q, k, v as in the MFMA launchers; dq, dk rows of stride ld_dq, ld_dk
+hipError_t launch_attn_fwd_f32(const float* q, int ldq, uint32_t q_elems, const float* kv, int ldkv, uint32_t kv_elems,
+                               float* O, float* lse, int B, int Sq, int Skv, int H, int D, hipStream_t st);
+hipError_t launch_attn_bwd_f32(const float* q, int ldq, uint32_t q_elems, const float* kv, int ldkv, uint32_t kv_elems,
+                               const float* dO, const float* lse, const float* delta, float* dq, int ld_dq, float* dk,
+                               int ld_dk, int B, int Sq, int Skv, int H, int D, hipStream_t st);
 hipError_t launch_xattn_fwd(int dtype, const void* q, const void* kv, void* O, float* lse, int B, int Sq, int Skv,
                             int H, int D, hipStream_t st);
 hipError_t launch_xattn_bwd(int dtype, const void* q, const void* kv, const void* O, const void* dO, const float* lse,
