@@ -279,16 +279,39 @@ SR_DEV TileId xcd_tile_id() {
   return {l % nb, (l / nb) % nh, l / (nb * nh)};
 }
 
+// Split calls: the streamed dimension is cut into nsplit runs of whole tiles, one workgroup each (run
+// outermost in the block index), so that a few heads still occupy the chip.  Partial results go to
+// fp32 planes, which one further kernel adds in run order.
+struct Run {
+  int blk, sp, t0, t1;   // row block, run, its tiles [t0, t1)
+};
+template <bool SPLIT>
+SR_DEV Run run_of(int blk, int nsplit, int nt) {
+  if constexpr (!SPLIT) return {blk, 0, 0, nt};
+  const int nblk = gridDim.x / nsplit, sp = blk / nblk, per = (nt + nsplit - 1) / nsplit;
+  return {blk - sp * nblk, sp, sp * per, min(nt, (sp + 1) * per)};
+}
+// A wave's transposed result to fp32 row `dst` of lane l32 (acc[db][r] = X[32 db + srow(r)][l32]).
+template <int HD>
+SR_DEV void store_part(float* dst, const f32x16 acc[HD / 32], int h32) {
+#pragma unroll
+  for (int db = 0; db < HD / 32; ++db)
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      *reinterpret_cast<f32x4*>(dst + 32 * db + 8 * g + 4 * h32) =
+          f32x4{acc[db][4 * g], acc[db][4 * g + 1], acc[db][4 * g + 2], acc[db][4 * g + 3]};
+}
+
 // ------------------------------------------------------------------------------ forward
 
 // NW waves (32 queries each) per workgroup share the K / V tiles.
 // Queries: Sq rows of q (row stride ldq); keys: Skv rows of kv (row stride ldkv), values D
 // columns after the keys; kv_elems: elements addressable from kv (the buffer's extent).
-template <int HD, int NW>
+template <int HD, int NW, bool SPLIT>
 __global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_fwd_mfma(const bf16_t* __restrict__ q, int ldq,
                                                      const bf16_t* __restrict__ kv, int ldkv, uint32_t kv_elems,
                                                      bf16_t* __restrict__ O, float* __restrict__ lse, int Sq, int Skv,
-                                                     int H, int D, float sl2) {
+                                                     int H, int D, float sl2, int nsplit, AttnPart part) {
   using G = Geo<HD>;
   constexpr int TE = G::TE, TB = G::TB, SGB = G::SGB, KS = G::KS, DB = G::DB;
   __shared__ __attribute__((aligned(16))) bf16_t smem[NSTG * 2 * TE];   // stage: K tile, V tile
@@ -296,8 +319,9 @@ __global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_fwd_mfma(const
   const TileId id = xcd_tile_id();
   const int b = id.b, hh = id.h;
   const bf16_t* qp = q + (size_t)b * Sq * ldq + hh * HD;
-  const int myq = id.blk * (32 * NW) + wid * 32 + l32;
   const int nt = (Skv + KT - 1) / KT;
+  const Run run = run_of<SPLIT>(id.blk, nsplit, nt);
+  const int myq = run.blk * (32 * NW) + wid * 32 + l32;
   const bool ragged = Skv % KT != 0;
   const __amdgpu_buffer_rsrc_t rq = make_rsrc(kv, kv_elems * 2u);
   const uint32_t kbase = (uint32_t)(((size_t)b * Skv * ldkv + hh * HD) * 2);
@@ -313,8 +337,8 @@ __global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_fwd_mfma(const
 
   constexpr int kLoads = 2 * (G::BLK / NW);   // buffer loads per thread per tile (two tiles)
   auto load = [&](int t, int s) {
-    tile_load<HD, NW>(rq, kbase, (uint32_t)ldkv, t * KT, Skv, smem + s * 2 * TE, t < nt);
-    tile_load<HD, NW>(rq, vbase, (uint32_t)ldkv, t * KT, Skv, smem + s * 2 * TE + TE, t < nt);
+    tile_load<HD, NW>(rq, kbase, (uint32_t)ldkv, t * KT, Skv, smem + s * 2 * TE, t < run.t1);
+    tile_load<HD, NW>(rq, vbase, (uint32_t)ldkv, t * KT, Skv, smem + s * 2 * TE + TE, t < run.t1);
   };
   auto mask = [&](f32x16& sc, int k0) {   // keys past Skv do not exist
 #pragma unroll
@@ -423,8 +447,8 @@ __global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_fwd_mfma(const
       }
   };
 
-  load(0, 0);
-  load(1, 1);   // past the last tile: zeros (a uniform count of loads in flight)
+  load(run.t0, 0);
+  load(run.t0 + 1, 1);   // past the last tile: zeros (a uniform count of loads in flight)
   wait_vm_lgkm0<kLoads>();
   lds_barrier();
   auto tile = [&](int t, auto stg) {
@@ -449,28 +473,39 @@ __global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_fwd_mfma(const
     wait_vm_lgkm0<kLoads>();   // tile t+1 resident: only tile t+2's loads may still fly
     lds_barrier();             // ... for every wave, and every wave is done with tile t's stage
   };
-  int t = 0;
-  for (; t + NSTG <= nt; t += NSTG) {
+  int t = run.t0;
+  for (; t + NSTG <= run.t1; t += NSTG) {
     tile(t, IC<0>{});
     tile(t + 1, IC<1>{});
     tile(t + 2, IC<2>{});
   }
-  if (t < nt) tile(t, IC<0>{});
-  if (t + 1 < nt) tile(t + 1, IC<1>{});
+  if (t < run.t1) tile(t, IC<0>{});
+  if (t + 1 < run.t1) tile(t + 1, IC<1>{});
 
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();   // every wave is done with the stages before they hold the output
   const float l_tot = half_pair_sum(lsum[0]);   // the second half's element is zero
+  if constexpr (SPLIT) {   // unnormalised O, its reference max and denominator
+    if (myq < Sq) {
+      store_part<HD>(part.p[run.sp] + ((size_t)b * Sq + myq) * D + hh * HD, o, h32);
+      if (h32 == 0) {
+        float* ml = part.ml + ((((size_t)run.sp * gridDim.z + b) * H + hh) * Sq + myq) * 2;
+        ml[0] = m_run * sl2;
+        ml[1] = l_tot;
+      }
+    }
+    return;
+  }
   if (h32 == 0 && myq < Sq) lse[((size_t)b * H + hh) * Sq + myq] = m_run * sl2 + log2f(l_tot);
   stage_t<HD>(smem, o, 1.0f / l_tot, wid, lane);
   __syncthreads();
-  unstage<HD, NW>(smem, O + (size_t)b * Sq * D + hh * HD, D, id.blk * (32 * NW), Sq);
+  unstage<HD, NW>(smem, O + (size_t)b * Sq * D + hh * HD, D, run.blk * (32 * NW), Sq);
 }
 
 // ------------------------------------------------------------------------------ backward dK, dV
 
 // NW waves (32 keys each) per workgroup share the Q / dO tiles.
-template <int HD, int NW>
+template <int HD, int NW, bool SPLIT>
 // Keys: Skv rows of kv (stride ldkv, values D columns on); queries: Sq rows of q (stride ldq,
 // q_elems addressable elements); dK to dk_out (stride ldo), dV D columns after it.
 __global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_bwd_dkv_mfma(const bf16_t* __restrict__ q, int ldq,
@@ -478,7 +513,7 @@ __global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_bwd_dkv_mfma(c
                                                          const bf16_t* __restrict__ dO,
                                                          const float* __restrict__ lse, const float* __restrict__ delta,
                                                          bf16_t* __restrict__ dk_out, int ldo, int Sq, int Skv, int H,
-                                                         int D, float sl2, float scale) {
+                                                         int D, float sl2, float scale, int nsplit, AttnPart part) {
   using G = Geo<HD>;
   constexpr int TE = G::TE, KS = G::KS, DB = G::DB;
   __shared__ __attribute__((aligned(16))) bf16_t smem[NSTG * 2 * TE];   // stage: Q tile, dO tile
@@ -488,8 +523,9 @@ __global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_bwd_dkv_mfma(c
   const int b = id.b, hh = id.h;
   const bf16_t* kp = kv + (size_t)b * Skv * ldkv + hh * HD;
   const bf16_t* vp = kp + D;
-  const int mykey = id.blk * (32 * NW) + wid * 32 + l32;
   const int nt = (Sq + KT - 1) / KT;
+  const Run run = run_of<SPLIT>(id.blk, nsplit, nt);
+  const int mykey = run.blk * (32 * NW) + wid * 32 + l32;
   const bool ragged = Sq % KT != 0;
 
   // K and -V fragments of the wave's keys (V negated: dP - Delta is then accumulated as
@@ -588,8 +624,8 @@ __global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_bwd_dkv_mfma(c
       }
   };
 
-  load(0, 0);
-  if (nt > 1) load(1, 1);
+  load(run.t0, 0);
+  if (run.t0 + 1 < run.t1) load(run.t0 + 1, 1);
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   auto tile = [&](int t, auto stg) {
@@ -605,27 +641,35 @@ __global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_bwd_dkv_mfma(c
     }
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();   // tile t+1 resident; tile t's stage no longer read
-    if (t + 2 < nt) load(t + 2, s2);
+    if (t + 2 < run.t1) load(t + 2, s2);
   };
-  int t = 0;
-  for (; t + NSTG <= nt; t += NSTG) {
+  int t = run.t0;
+  for (; t + NSTG <= run.t1; t += NSTG) {
     tile(t, IC<0>{});
     tile(t + 1, IC<1>{});
     tile(t + 2, IC<2>{});
   }
-  if (t < nt) tile(t, IC<0>{});
-  if (t + 1 < nt) tile(t + 1, IC<1>{});
+  if (t < run.t1) tile(t, IC<0>{});
+  if (t + 1 < run.t1) tile(t + 1, IC<1>{});
 
   __builtin_amdgcn_s_waitcnt(0);
+  if constexpr (SPLIT) {   // fp32 planes of 3 D columns laid out as qkv
+    if (mykey < Skv) {
+      float* row = part.p[run.sp] + ((size_t)b * Skv + mykey) * 3 * D + D + hh * HD;
+      store_part<HD>(row, dk, h32);
+      store_part<HD>(row + D, dv, h32);
+    }
+    return;
+  }
   __syncthreads();
   bf16_t* out = dk_out + (size_t)b * Skv * ldo;
   stage_t<HD>(smem, dk, scale, wid, lane);
   __syncthreads();
-  unstage<HD, NW>(smem, out + hh * HD, ldo, id.blk * (32 * NW), Skv);
+  unstage<HD, NW>(smem, out + hh * HD, ldo, run.blk * (32 * NW), Skv);
   __syncthreads();
   stage_t<HD>(smem, dv, 1.0f, wid, lane);
   __syncthreads();
-  unstage<HD, NW>(smem, out + D + hh * HD, ldo, id.blk * (32 * NW), Skv);
+  unstage<HD, NW>(smem, out + D + hh * HD, ldo, run.blk * (32 * NW), Skv);
 }
 
 // ------------------------------------------------------ backward dK, dV at head dim 128: one wave per SIMD
@@ -1013,7 +1057,7 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_h128(const bf16_t* __rest
 // ------------------------------------------------------------------------------ backward dQ
 
 // NW waves (32 queries each) per workgroup share the K / V tiles.
-template <int HD, int NW>
+template <int HD, int NW, bool SPLIT>
 // Queries: Sq rows of q (stride ldq); keys: Skv rows of kv (stride ldkv, kv_elems addressable
 // elements, values D columns on); dQ to dq_out (stride ldo).
 __global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_bwd_dq_mfma(const bf16_t* __restrict__ q, int ldq,
@@ -1021,7 +1065,7 @@ __global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_bwd_dq_mfma(co
                                                         const bf16_t* __restrict__ dO,
                                                         const float* __restrict__ lse, const float* __restrict__ delta,
                                                         bf16_t* __restrict__ dq_out, int ldo, int Sq, int Skv, int H,
-                                                        int D, float sl2, float scale) {
+                                                        int D, float sl2, float scale, int nsplit, AttnPart part) {
   using G = Geo<HD>;
   constexpr int TE = G::TE, TB = G::TB, SGB = G::SGB, KS = G::KS, DB = G::DB;
   __shared__ __attribute__((aligned(16))) bf16_t smem[NSTG * 2 * TE];   // stage: K tile, V tile
@@ -1030,8 +1074,9 @@ __global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_bwd_dq_mfma(co
   const int b = id.b, hh = id.h;
   const bf16_t* qp = q + (size_t)b * Sq * ldq + hh * HD;
   const bf16_t* dop = dO + (size_t)b * Sq * D + hh * HD;
-  const int myq = id.blk * (32 * NW) + wid * 32 + l32;
   const int nt = (Skv + KT - 1) / KT;
+  const Run run = run_of<SPLIT>(id.blk, nsplit, nt);
+  const int myq = run.blk * (32 * NW) + wid * 32 + l32;
   const bool ragged = Skv % KT != 0;
 
   // Q and -dO fragments of the wave's queries (dO negated: dP - Delta is then accumulated as
@@ -1060,8 +1105,8 @@ __global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_bwd_dq_mfma(co
   ta.init(lds_addr(smem), lane);
   constexpr int kLoads = 2 * (G::BLK / NW);   // buffer loads per thread per tile (two tiles)
   auto load = [&](int t, int s) {
-    tile_load<HD, NW>(rq, kbase, (uint32_t)ldkv, t * KT, Skv, smem + s * 2 * TE, t < nt);
-    tile_load<HD, NW>(rq, vbase, (uint32_t)ldkv, t * KT, Skv, smem + s * 2 * TE + TE, t < nt);
+    tile_load<HD, NW>(rq, kbase, (uint32_t)ldkv, t * KT, Skv, smem + s * 2 * TE, t < run.t1);
+    tile_load<HD, NW>(rq, vbase, (uint32_t)ldkv, t * KT, Skv, smem + s * 2 * TE + TE, t < run.t1);
   };
   // K (tile 0) or V (tile 1) row fragments of key unit U of stage SG
   auto read_rows = [&](auto sg, auto uu, auto tl, RawFrag<true> (&fr)[KS]) {
@@ -1115,8 +1160,8 @@ __global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_bwd_dq_mfma(co
       }
   };
 
-  load(0, 0);
-  load(1, 1);   // past the last tile: zeros (a uniform count of loads in flight)
+  load(run.t0, 0);
+  load(run.t0 + 1, 1);   // past the last tile: zeros (a uniform count of loads in flight)
   wait_vm_lgkm0<kLoads>();
   lds_barrier();
   auto tile = [&](int t, auto stg) {
@@ -1146,20 +1191,24 @@ __global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_bwd_dq_mfma(co
     wait_vm_lgkm0<kLoads>();   // tile t+1 resident: only tile t+2's loads may still fly
     lds_barrier();             // ... for every wave, and every wave is done with tile t's stage
   };
-  int t = 0;
-  for (; t + NSTG <= nt; t += NSTG) {
+  int t = run.t0;
+  for (; t + NSTG <= run.t1; t += NSTG) {
     tile(t, IC<0>{});
     tile(t + 1, IC<1>{});
     tile(t + 2, IC<2>{});
   }
-  if (t < nt) tile(t, IC<0>{});
-  if (t + 1 < nt) tile(t + 1, IC<1>{});
+  if (t < run.t1) tile(t, IC<0>{});
+  if (t + 1 < run.t1) tile(t + 1, IC<1>{});
 
-  __builtin_amdgcn_s_waitcnt(0);
+  __builtin_amdgcn_s_waitcnt(0);   // no fill may land after the workgroup's LDS is given away
+  if constexpr (SPLIT) {
+    if (myq < Sq) store_part<HD>(part.p[run.sp] + ((size_t)b * Sq + myq) * 3 * D + hh * HD, dq, h32);
+    return;
+  }
   __syncthreads();
   stage_t<HD>(smem, dq, scale, wid, lane);
   __syncthreads();
-  unstage<HD, NW>(smem, dq_out + (size_t)b * Sq * ldo + hh * HD, ldo, id.blk * (32 * NW), Sq);
+  unstage<HD, NW>(smem, dq_out + (size_t)b * Sq * ldo + hh * HD, ldo, run.blk * (32 * NW), Sq);
 }
 
 // ------------------------------------------------------------ backward dQ at head dim 128: one wave per SIMD
@@ -1727,6 +1776,67 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_h128(const bf16_t* __restrict
   unstage<HD, NW>(smem, O + (size_t)b * Sq * D + hh * HD, D, id.blk * (32 * NW), Sq);
 }
 
+// ------------------------------------------------------------------------- split calls: combination
+// O = sum_s 2^(m_s - M) o_s / sum_s 2^(m_s - M) l_s over the runs in order, lse = M + log2 of the
+// denominator; four columns per thread.
+template <int HD>
+__global__ __launch_bounds__(256) void attn_combine_fwd(AttnPart part, int nsplit, bf16_t* __restrict__ O,
+                                                        float* __restrict__ lse, int B, int S, int H, int D) {
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= (size_t)B * S * D / 4) return;
+  const int row = (int)(i / (D / 4)), c = (int)(i % (D / 4)) * 4;
+  const int b = row / S, q = row - b * S, hh = c / HD;
+  const size_t st = ((size_t)b * H + hh) * S + q;
+  float m[kMaxSplit], l[kMaxSplit], mx = -INFINITY;
+  f32x4 o[kMaxSplit];
+#pragma unroll
+  for (int s = 0; s < kMaxSplit; ++s)
+    if (s < nsplit) {
+      const float* ml = part.ml + ((size_t)s * B * H * S + st) * 2;
+      m[s] = ml[0];
+      l[s] = ml[1];
+      o[s] = *reinterpret_cast<const f32x4*>(part.p[s] + (size_t)row * D + c);
+    }
+#pragma unroll
+  for (int s = 0; s < kMaxSplit; ++s)
+    if (s < nsplit) mx = fmaxf(mx, m[s]);
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  float den = 0.f;
+#pragma unroll
+  for (int s = 0; s < kMaxSplit; ++s)
+    if (s < nsplit) {
+      const float w = ex2(m[s] - mx);
+      acc += o[s] * w;
+      den += l[s] * w;
+    }
+  const float inv = 1.0f / den;
+  i32x2 out;
+  out[0] = (int)f2bf2(acc[0] * inv, acc[1] * inv);
+  out[1] = (int)f2bf2(acc[2] * inv, acc[3] * inv);
+  *reinterpret_cast<i32x2*>(O + (size_t)row * D + c) = out;
+  if (c % HD == 0) lse[st] = mx + log2f(den);
+}
+
+// dqkv = the planes of 3 D columns added in run order, dq and dk scaled; four columns per thread.
+__global__ __launch_bounds__(256) void attn_combine_bwd(AttnPart part, int nsplit, bf16_t* __restrict__ dqkv, size_t n4,
+                                                        int D, float scale) {
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n4) return;
+  f32x4 v[kMaxSplit];
+#pragma unroll
+  for (int s = 0; s < kMaxSplit; ++s)
+    if (s < nsplit) v[s] = reinterpret_cast<const f32x4*>(part.p[s])[i];
+  f32x4 acc = v[0];
+#pragma unroll
+  for (int s = 1; s < kMaxSplit; ++s)
+    if (s < nsplit) acc += v[s];
+  const float mul = (int)(i % (3 * D / 4)) < D / 2 ? scale : 1.0f;
+  i32x2 out;
+  out[0] = (int)f2bf2(acc[0] * mul, acc[1] * mul);
+  out[1] = (int)f2bf2(acc[2] * mul, acc[3] * mul);
+  reinterpret_cast<i32x2*>(dqkv)[i] = out;
+}
+
 // ------------------------------------------------------------------------- column sums
 // colsum[b,h,j] = sum over the S queries i of P[i,j], P = exp2(s * sl2 - lse) the forward's
 // probabilities: the attention token j receives in head h.  MFMA: the dK/dV kernel's score
@@ -1840,27 +1950,50 @@ __global__ __launch_bounds__(64) void attn_colsum_simple(const Ta* __restrict__ 
 
 static inline float attn_sl2(int hd) { return 1.4426950408889634f / sqrtf((float)hd); }
 
-bool attn_uses_mfma(int dtype, int hd) { return dtype == kBF16 && (hd == 32 || hd == 64 || hd == 128); }
-
 #define SR_TRY_HIP(x)                 \
   do {                                \
     hipError_t e_ = (x);              \
     if (e_ != hipSuccess) return e_;  \
   } while (0)
 
+// Runs per call.  A grid that leaves CUs without a workgroup (one workgroup of eight waves per CU at
+// head dim 64, two of four at head dim 32) is multiplied by cutting the streamed dimension, into runs
+// of at least eight tiles: below that a run's start and the combination cost what the cut saves.
+// 4050 tokens, combination included: four heads of 64 (64 workgroups, four runs) forward 71 -> 33,
+// dK/dV 112 -> 46, dQ 81 -> 32, combination 9 us; four heads of 32 (128 workgroups, four runs) 59 ->
+// 35, 94 -> 46, 60 -> 29, 9 us.
+// At head dim 128 the register-explicit kernels stay uncut (their models have eight heads or more).
+int attn_splits(int dtype, int B, int S, int H, int hd, int cap) {
+  if (dtype != kBF16 || hd == 128) return 1;
+  const int rows = 32 * (hd == 64 ? attn_waves<64>() : attn_waves<32>());
+  const long wgs = (long)((S + rows - 1) / rows) * H * B;
+  const int nt = (S + KT - 1) / KT;
+  const int n = (int)std::min<long>(std::min(cap, kMaxSplit), std::min<long>((hd == 64 ? 256 : 512) / wgs, nt / 8));
+  if (n < 2) return 1;
+  const int per = (nt + n - 1) / n;
+  return (nt + per - 1) / per;   // no empty run
+}
+
 // The MFMA kernels on Sq query rows and Skv key/value rows (self-attention: both S, q, k and v
-// in one token-major qkv buffer; asymmetric attention: separate buffers).
+// in one token-major qkv buffer; asymmetric attention: separate buffers, never split).
 template <int HD>
 static hipError_t fwd_mfma_hd(const bf16_t* q, int ldq, const bf16_t* kv, int ldkv, uint32_t kv_elems, bf16_t* O,
-                              float* lse, int B, int Sq, int Skv, int H, int D, hipStream_t st) {
+                              float* lse, int B, int Sq, int Skv, int H, int D, hipStream_t st, int nsplit = 1,
+                              AttnPart part = {}) {
   constexpr int kw = attn_waves<HD>();
-  dim3 g((Sq + 32 * kw - 1) / (32 * kw), H, B);
-  if constexpr (HD == 128)
+  dim3 g((Sq + 32 * kw - 1) / (32 * kw) * nsplit, H, B);
+  if constexpr (HD == 128) {
     SR_LAUNCH(attn_fwd_h128, g, dim3(64 * kw), 0, st, q, ldq, kv, ldkv, kv_elems, O, lse, Sq, Skv, H, D,
                        attn_sl2(HD));
-  else
-    SR_LAUNCH((attn_fwd_mfma<HD, kw>), g, dim3(64 * kw), 0, st, q, ldq, kv, ldkv, kv_elems, O, lse, Sq, Skv,
-                       H, D, attn_sl2(HD));
+  } else if (nsplit > 1) {
+    SR_LAUNCH((attn_fwd_mfma<HD, kw, true>), g, dim3(64 * kw), 0, st, q, ldq, kv, ldkv, kv_elems, O, lse, Sq, Skv, H,
+              D, attn_sl2(HD), nsplit, part);
+    SR_LAUNCH(attn_combine_fwd<HD>, dim3((unsigned)(((size_t)B * Sq * D / 4 + 255) / 256)), dim3(256), 0, st, part,
+              nsplit, O, lse, B, Sq, H, D);
+  } else {
+    SR_LAUNCH((attn_fwd_mfma<HD, kw, false>), g, dim3(64 * kw), 0, st, q, ldq, kv, ldkv, kv_elems, O, lse, Sq, Skv, H,
+              D, attn_sl2(HD), 1, part);
+  }
   return hipGetLastError();
 }
 
@@ -1874,15 +2007,19 @@ hipError_t launch_attn_fwd_mfma(const bf16_t* q, int ldq, const bf16_t* kv, int 
 template <int HD>
 static hipError_t dkv_mfma_hd(const bf16_t* q, int ldq, uint32_t q_elems, const bf16_t* kv, int ldkv,
                               const bf16_t* dO, const float* lse, const float* delta, bf16_t* dk_out, int ldo, int B,
-                              int Sq, int Skv, int H, int D, hipStream_t st) {
+                              int Sq, int Skv, int H, int D, hipStream_t st, int nsplit = 1, AttnPart part = {}) {
   constexpr int kw = attn_waves<HD>();
-  dim3 g((Skv + 32 * kw - 1) / (32 * kw), H, B);
+  dim3 g((Skv + 32 * kw - 1) / (32 * kw) * nsplit, H, B);
+  const float scale = 1.0f / sqrtf((float)HD);
   if constexpr (HD == 128)
     SR_LAUNCH(attn_bwd_dkv_h128, g, dim3(64 * kw), 0, st, q, ldq, q_elems, kv, ldkv, dO, lse, delta, dk_out,
-                       ldo, Sq, Skv, H, D, attn_sl2(HD), 1.0f / sqrtf((float)HD));
+                       ldo, Sq, Skv, H, D, attn_sl2(HD), scale);
+  else if (nsplit > 1)
+    SR_LAUNCH((attn_bwd_dkv_mfma<HD, kw, true>), g, dim3(64 * kw), 0, st, q, ldq, q_elems, kv, ldkv, dO, lse, delta,
+              dk_out, ldo, Sq, Skv, H, D, attn_sl2(HD), scale, nsplit, part);
   else
-    SR_LAUNCH((attn_bwd_dkv_mfma<HD, kw>), g, dim3(64 * kw), 0, st, q, ldq, q_elems, kv, ldkv, dO, lse,
-                       delta, dk_out, ldo, Sq, Skv, H, D, attn_sl2(HD), 1.0f / sqrtf((float)HD));
+    SR_LAUNCH((attn_bwd_dkv_mfma<HD, kw, false>), g, dim3(64 * kw), 0, st, q, ldq, q_elems, kv, ldkv, dO, lse, delta,
+              dk_out, ldo, Sq, Skv, H, D, attn_sl2(HD), scale, 1, part);
   return hipGetLastError();
 }
 
@@ -1891,22 +2028,27 @@ hipError_t launch_attn_dkv_mfma(const bf16_t* q, int ldq, uint32_t q_elems, cons
                                 int Sq, int Skv, int H, int D, hipStream_t st) {
   if (D / H == 128)
     return dkv_mfma_hd<128>(q, ldq, q_elems, kv, ldkv, dO, lse, delta, dk_out, ldo, B, Sq, Skv, H, D, st);
-  if (D / H == 32) return dkv_mfma_hd<32>(q, ldq, q_elems, kv, ldkv, dO, lse, delta, dk_out, ldo, B, Sq, Skv, H, D, st);
+  if (D / H == 32)
+    return dkv_mfma_hd<32>(q, ldq, q_elems, kv, ldkv, dO, lse, delta, dk_out, ldo, B, Sq, Skv, H, D, st);
   return dkv_mfma_hd<64>(q, ldq, q_elems, kv, ldkv, dO, lse, delta, dk_out, ldo, B, Sq, Skv, H, D, st);
 }
 
 template <int HD>
 static hipError_t dq_mfma_hd(const bf16_t* q, int ldq, const bf16_t* kv, int ldkv, uint32_t kv_elems,
                              const bf16_t* dO, const float* lse, const float* delta, bf16_t* dq_out, int ldo, int B,
-                             int Sq, int Skv, int H, int D, hipStream_t st) {
+                             int Sq, int Skv, int H, int D, hipStream_t st, int nsplit = 1, AttnPart part = {}) {
   constexpr int kw = attn_waves<HD>();
-  dim3 g((Sq + 32 * kw - 1) / (32 * kw), H, B);
+  dim3 g((Sq + 32 * kw - 1) / (32 * kw) * nsplit, H, B);
+  const float scale = 1.0f / sqrtf((float)HD);
   if constexpr (HD == 128)
     SR_LAUNCH(attn_bwd_dq_h128, g, dim3(64 * kw), 0, st, q, ldq, kv, ldkv, kv_elems, dO, lse, delta, dq_out,
-                       ldo, Sq, Skv, H, D, attn_sl2(HD), 1.0f / sqrtf((float)HD));
+                       ldo, Sq, Skv, H, D, attn_sl2(HD), scale);
+  else if (nsplit > 1)
+    SR_LAUNCH((attn_bwd_dq_mfma<HD, kw, true>), g, dim3(64 * kw), 0, st, q, ldq, kv, ldkv, kv_elems, dO, lse, delta,
+              dq_out, ldo, Sq, Skv, H, D, attn_sl2(HD), scale, nsplit, part);
   else
-    SR_LAUNCH((attn_bwd_dq_mfma<HD, kw>), g, dim3(64 * kw), 0, st, q, ldq, kv, ldkv, kv_elems, dO, lse,
-                       delta, dq_out, ldo, Sq, Skv, H, D, attn_sl2(HD), 1.0f / sqrtf((float)HD));
+    SR_LAUNCH((attn_bwd_dq_mfma<HD, kw, false>), g, dim3(64 * kw), 0, st, q, ldq, kv, ldkv, kv_elems, dO, lse, delta,
+              dq_out, ldo, Sq, Skv, H, D, attn_sl2(HD), scale, 1, part);
   return hipGetLastError();
 }
 
@@ -1915,44 +2057,57 @@ hipError_t launch_attn_dq_mfma(const bf16_t* q, int ldq, const bf16_t* kv, int l
                                int Sq, int Skv, int H, int D, hipStream_t st) {
   if (D / H == 128)
     return dq_mfma_hd<128>(q, ldq, kv, ldkv, kv_elems, dO, lse, delta, dq_out, ldo, B, Sq, Skv, H, D, st);
-  if (D / H == 32) return dq_mfma_hd<32>(q, ldq, kv, ldkv, kv_elems, dO, lse, delta, dq_out, ldo, B, Sq, Skv, H, D, st);
+  if (D / H == 32)
+    return dq_mfma_hd<32>(q, ldq, kv, ldkv, kv_elems, dO, lse, delta, dq_out, ldo, B, Sq, Skv, H, D, st);
   return dq_mfma_hd<64>(q, ldq, kv, ldkv, kv_elems, dO, lse, delta, dq_out, ldo, B, Sq, Skv, H, D, st);
 }
 
 hipError_t launch_attn_fwd(int dtype, const void* qkv, void* O, float* lse, int B, int S, int H, int D,
-                           hipStream_t st) {
-  const int hd = D / H;
-  if (attn_uses_mfma(dtype, hd)) {
+                           hipStream_t st, int nsplit, const AttnPart& part) {
+  if (dtype == kBF16) {
     const bf16_t* q = (const bf16_t*)qkv;
-    return launch_attn_fwd_mfma(q, 3 * D, q + D, 3 * D, (uint32_t)((size_t)B * S * 3 * D - D), (bf16_t*)O, lse, B,
-                                S, S, H, D, st);
+    const uint32_t kv_elems = (uint32_t)((size_t)B * S * 3 * D - D);
+    auto run = [&](auto hd) {
+      return fwd_mfma_hd<decltype(hd)::value>(q, 3 * D, q + D, 3 * D, kv_elems, (bf16_t*)O, lse, B, S, S, H, D, st,
+                                              nsplit, part);
+    };
+    return D / H == 128 ? run(IC<128>{}) : D / H == 32 ? run(IC<32>{}) : run(IC<64>{});
   }
   const float* q = (const float*)qkv;
   const uint32_t all = (uint32_t)((size_t)B * S * 3 * D);
   return launch_attn_fwd_f32(q, 3 * D, all, q + D, 3 * D, all - D, (float*)O, lse, B, S, S, H, D, st);
 }
 
+template <int HD>
+static hipError_t bwd_mfma_hd(const bf16_t* qkv, const bf16_t* dO, const float* lse, const float* delta, bf16_t* dqkv,
+                              int B, int S, int H, int D, hipStream_t st, int nsplit, const AttnPart& part) {
+  const double units = 2.0 * B * (double)S * S * D;   // one S x S x hd product over all heads
+  const uint32_t all = (uint32_t)((size_t)B * S * 3 * D);
+  {
+    // algorithmic: dP, dV, dK (the recomputed scores are not counted)
+    ProfScope ps("attn_bwd_dkv", 3 * units, (double)B * S * D * 2 * 6, st);
+    SR_TRY_HIP(dkv_mfma_hd<HD>(qkv, 3 * D, all, qkv + D, 3 * D, dO, lse, delta, dqkv + D, 3 * D, B, S, S, H, D, st,
+                               nsplit, part));
+  }
+  ProfScope ps("attn_bwd_dq", units, (double)B * S * D * 2 * 5, st);
+  SR_TRY_HIP(dq_mfma_hd<HD>(qkv, 3 * D, qkv + D, 3 * D, all - D, dO, lse, delta, dqkv, 3 * D, B, S, S, H, D, st,
+                            nsplit, part));
+  if (nsplit > 1) {
+    const size_t n4 = (size_t)B * S * 3 * D / 4;
+    SR_LAUNCH(attn_combine_bwd, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st, part, nsplit, dqkv, n4, D,
+              1.0f / sqrtf((float)HD));
+  }
+  return hipGetLastError();
+}
+
 hipError_t launch_attn_bwd(int dtype, const void* qkv, const void* dO, const float* lse, const float* delta,
-                           void* dqkv, int B, int S, int H, int D, hipStream_t st) {
-  const int hd = D / H;
-  if (attn_uses_mfma(dtype, hd)) {
-    const float sl2 = attn_sl2(hd), sc = 1.0f / sqrtf((float)hd);
-    const double units = 2.0 * B * (double)S * S * D;   // one S x S x hd product over all heads
-    const bf16_t* q = (const bf16_t*)qkv;
-    const uint32_t all = (uint32_t)((size_t)B * S * 3 * D);
-    {
-      // algorithmic: dP, dV, dK (the recomputed scores are not counted)
-      ProfScope ps("attn_bwd_dkv", 3 * units, (double)B * S * D * 2 * 6, st);
-      SR_TRY_HIP(launch_attn_dkv_mfma(q, 3 * D, all, q + D, 3 * D, (const bf16_t*)dO, lse, delta, (bf16_t*)dqkv + D,
-                                      3 * D, B, S, S, H, D, st));
-    }
-    {
-      ProfScope ps("attn_bwd_dq", units, (double)B * S * D * 2 * 5, st);
-      SR_TRY_HIP(launch_attn_dq_mfma(q, 3 * D, q + D, 3 * D, all - D, (const bf16_t*)dO, lse, delta, (bf16_t*)dqkv,
-                                     3 * D, B, S, S, H, D, st));
-    }
-    (void)sl2; (void)sc;
-    return hipSuccess;
+                           void* dqkv, int B, int S, int H, int D, hipStream_t st, int nsplit, const AttnPart& part) {
+  if (dtype == kBF16) {
+    auto run = [&](auto hd) {
+      return bwd_mfma_hd<decltype(hd)::value>((const bf16_t*)qkv, (const bf16_t*)dO, lse, delta, (bf16_t*)dqkv, B, S,
+                                              H, D, st, nsplit, part);
+    };
+    return D / H == 128 ? run(IC<128>{}) : D / H == 32 ? run(IC<32>{}) : run(IC<64>{});
   }
   ProfScope ps("attn_bwd_generic", 8.0 * B * (double)S * S * D, 0, st);
   const float* q = (const float*)qkv;

@@ -16,7 +16,7 @@ namespace sr {
 
 hipError_t launch_xattn_fwd(int dtype, const void* q, const void* kv, void* O, float* lse, int B, int Sq, int Skv,
                             int H, int D, hipStream_t st) {
-  if (attn_uses_mfma(dtype, D / H))
+  if (dtype == kBF16)
     return launch_attn_fwd_mfma((const bf16_t*)q, D, (const bf16_t*)kv, 2 * D, (uint32_t)((size_t)B * Skv * 2 * D),
                                 (bf16_t*)O, lse, B, Sq, Skv, H, D, st);
   return launch_attn_fwd_f32((const float*)q, D, (uint32_t)((size_t)B * Sq * D), (const float*)kv, 2 * D,
@@ -27,7 +27,7 @@ hipError_t launch_xattn_bwd(int dtype, const void* q, const void* kv, const void
                             float* delta, void* dq, void* dkv, int B, int Sq, int Skv, int H, int D, hipStream_t st) {
   hipError_t e = launch_attn_delta(dtype, dO, O, B, Sq, H, D / H, delta, st);
   if (e != hipSuccess) return e;
-  if (attn_uses_mfma(dtype, D / H)) {
+  if (dtype == kBF16) {
     const bf16_t *qb = (const bf16_t*)q, *kvb = (const bf16_t*)kv, *dOb = (const bf16_t*)dO;
     e = launch_attn_dkv_mfma(qb, D, (uint32_t)((size_t)B * Sq * D), kvb, 2 * D, dOb, lse, delta, (bf16_t*)dkv, 2 * D, B,
                              Sq, Skv, H, D, st);

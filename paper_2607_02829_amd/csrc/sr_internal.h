@@ -179,9 +179,17 @@ hipError_t launch_weight_grad(const GemmDesc& g, float* dw, float* db, float* pa
 hipError_t launch_reduce_jobs(const ReduceJob* jobs, int njobs, hipStream_t st);
 void weight_grad_scratch(int M, int N, int K, size_t* part_floats, size_t* dbpart_floats);
 
-bool attn_uses_mfma(int dtype, int hd);
+// Self-attention whose grid would leave CUs idle cuts the streamed dimension into runs (attn_splits,
+// at most cap of them).  Each run writes fp32 planes: forward p[run] of [B*S, D] and ml of
+// [run][B, H, S][2] (reference max, denominator); backward p[run] of [B*S, 3 D].
+constexpr int kMaxSplit = 4;
+struct AttnPart {
+  float* p[kMaxSplit] = {};
+  float* ml = nullptr;
+};
+int attn_splits(int dtype, int B, int S, int H, int hd, int cap);
 hipError_t launch_attn_fwd(int dtype, const void* qkv, void* O, float* lse, int B, int S, int H, int D,
-                           hipStream_t st);
+                           hipStream_t st, int nsplit = 1, const AttnPart& part = {});
 hipError_t launch_attn_colsum(int dtype, const void* qkv, const float* lse, float* colsum, int B, int S, int H, int D,
                               hipStream_t st);
 // bf16 operands as their 16-bit patterns
@@ -204,6 +212,7 @@ hipError_t launch_xattn_fwd(int dtype, const void* q, const void* kv, void* O, f
 hipError_t launch_xattn_bwd(int dtype, const void* q, const void* kv, const void* O, const void* dO, const float* lse,
                             float* delta, void* dq, void* dkv, int B, int Sq, int Skv, int H, int D, hipStream_t st);
 hipError_t launch_attn_bwd(int dtype, const void* qkv, const void* dO, const float* lse, const float* delta,
-                           void* dqkv, int B, int S, int H, int D, hipStream_t st);
+                           void* dqkv, int B, int S, int H, int D, hipStream_t st, int nsplit = 1,
+                           const AttnPart& part = {});
 
 }  // namespace sr

@@ -140,8 +140,26 @@ size_t layout_scratch(const Dims& d, char* base, Scratch* out) {
   // recomputed operands of the weight-gradient GEMMs (written and read on the second stream)
   s.u_rc = c.take<void>(M * D * e);
   s.gz_rc = c.take<void>(M * F * e);
+  s.attn_splits = attn_splits(d.dtype, d.B, d.S, d.H, d.D / d.H, kMaxSplit);
+  if (s.attn_splits > 1)   // at most 256 workgroups' rows: 50 MB
+    for (int k = 0; k < s.attn_splits; ++k) s.attn.p[k] = c.take<float>(M * 3 * D * 4);
   if (out) *out = s;
   return c.off;
+}
+
+// Planes of a split attention forward, in buffers of the block that are written only after it: h1, z
+// and GELU(z), the maxima and denominators over u1 (read only before).  Returns the number of runs.
+static int fwd_attn_part(const Dims& d, const BlockSaved& s, AttnPart* part) {
+  const size_t plane = (size_t)d.M * d.D, act = (size_t)d.M * d.F * d.elt / 4 / plane * plane;
+  int n = 0;
+  auto add = [&](void* base, size_t floats) {
+    for (size_t o = 0; o + plane <= floats && n < kMaxSplit; o += plane) part->p[n++] = (float*)base + o;
+  };
+  add(s.h1, plane);
+  add(s.z, act);
+  add(s.gz, act);
+  part->ml = (float*)s.u1;   // 8 bytes per run, head and row in a row of 2 hd bytes per head
+  return attn_splits(d.dtype, d.B, d.S, d.H, d.D / d.H, n);
 }
 
 // ============================================================================ forward
@@ -183,7 +201,9 @@ hipError_t stack_fwd(const Dims& d, const sr_block_params* p, const void* cond, 
       }
       {
         ProfScope ps("attn_fwd", 4.0 * d.B * (double)S * S * D, (double)M * D * e * 4, st);
-        SR_TRY(launch_attn_fwd(d.dtype, s.qkv, s.O, s.lse, d.B, S, d.H, D, st));
+        AttnPart part;
+        const int runs = fwd_attn_part(d, s, &part);
+        SR_TRY(launch_attn_fwd(d.dtype, s.qkv, s.O, s.lse, d.B, S, d.H, D, st, runs, part));
       }
       {
         GemmDesc g = desc(d, s.O, true, D, (size_t)M * D * e, w.w_o, true, D, (size_t)D * D * e, M, D, D);
@@ -494,7 +514,7 @@ hipError_t stack_bwd(const Dims& d, const sr_block_params* p, const void* cond, 
       }
       SR_TRY(join(kQkv + par));   // dqkv[par] may still be read by dW_qkv two blocks back
       SR_TRY(fork_point([&]() -> hipError_t {
-        return launch_attn_bwd(d.dtype, s.qkv, sc.dO, s.lse, sc.delta, dqkv, d.B, S, d.H, D, st);
+        return launch_attn_bwd(d.dtype, s.qkv, sc.dO, s.lse, sc.delta, dqkv, d.B, S, d.H, D, st, sc.attn_splits, sc.attn);
       }));
       if (!ada) {   // LN2 of this block and LN1 of the block before it join the reduction launch
         if (g.ln2_w || g.ln2_b) jobs[4] = ln_job(sc.lnpart[0][par], g.ln2_w, g.ln2_b);

@@ -26,6 +26,8 @@ struct Scratch {
   // reductions can run as one launch after its last weight gradient.
   float *wpart[4], *dbpart[4];
   float *g_res, *g_res2, *du, *delta, *part, *lnpart[2][2], *dmod, *gvpart;
+  AttnPart attn;   // planes of a split attention backward
+  int attn_splits;
   void *g_act[2], *dz[2], *dO, *dqkv[2], *u_rc, *gz_rc;
 };
 
