@@ -7,12 +7,11 @@
 // dW = dY^T X is m-major x n-major (the reduction runs over tokens).
 //
 // gemm_mfma: bf16 operands, fp32 accumulation on gfx950 matrix cores
-// (v_mfma_f32_32x32x16_bf16).  Workgroup tile 128 x 128 x 64, four waves in a
-// 2 x 2 arrangement, each wave 64 x 64 = 2 x 2 MFMA tiles.  Operand tiles are
-// staged in LDS in k-contiguous rows with an XOR swizzle of the 16-byte chunks;
-// k-major operands go global -> LDS directly, m-major ones are transposed in
-// registers (4 x 8 blocks) on the way in.  The next k-tile is in flight while the
-// current one is consumed.
+// (v_mfma_f32_32x32x16_bf16).  Workgroup tiles of 128 x 128 down to 32 x 32 by 64 k,
+// four waves in a 2 x 2 arrangement on the larger ones; on the smaller ones two to eight
+// groups of waves share the k range (pick_shape).  Operand tiles go global -> LDS directly,
+// their 16-byte chunks at XOR-swizzled positions; m- and n-major ones are transposed by the
+// LDS read.  Two to four k-tiles are in flight while the current one is consumed.
 // Global loads go through buffer resources, so rows past the end of an operand
 // read as zero: ragged token counts need no predicates in the main loop.
 //
@@ -168,7 +167,7 @@ constexpr int KS = GK / 16;   // MFMA k-steps per tile
 SR_DEV int kswz(int r) { return (r ^ (r >> 3)) & 7; }
 template <int R>
 SR_DEV int rswz(int k) {
-  return R >= 128 ? (k & 3) << 2 : ((k >> 1) & 1) << 2;
+  return R >= 128 ? (k & 3) << 2 : R == 64 ? ((k >> 1) & 1) << 2 : 0;   // R = 32: four k-rows are 256 contiguous bytes
 }
 
 // One operand tile (R rows or r-columns, k0 .. k0+63) straight from global memory into LDS
@@ -178,9 +177,9 @@ SR_DEV int rswz(int k) {
 // computed once; a tile adds one wave-uniform byte offset (k0 * 2 for k-major operands,
 // k0 * ld * 2 for r-major ones), and the LDS block addresses are wave-uniform too, so a fill
 // costs one vector add per load.
-template <int R, bool KMAJ>
+template <int R, bool KMAJ, int NW>
 struct TileFill {
-  static constexpr int BPW = R / 32;   // the tile is R/8 blocks of 1 KB, four waves
+  static constexpr int BPW = R / 8 / NW;   // the tile is R/8 blocks of 1 KB, shared by NW waves
   uint32_t off[BPW];
   SR_DEV void init(int r0, int ld, int lane, int wid) {
 #pragma unroll
@@ -275,41 +274,54 @@ struct FragAddr {
   static constexpr int kReads = KMAJ ? NI : 2 * NI;   // LDS instructions per k-step
 };
 
-// BM x BN workgroup tile, four waves in 2 x 2, each (BM/2) x (BN/2) = MI x NJ MFMA tiles of
-// 32 x 32 (v_mfma_f32_32x32x16_bf16).  NST operand stages in LDS.  Per k-tile t: k-steps
+// BM x BN workgroup tile, WM x WN waves, each (BM/WM) x (BN/WN) = MI x NJ MFMA tiles of
+// 32 x 32 (v_mfma_f32_32x32x16_bf16).  KG such groups of waves share the tile: group g takes
+// the g-th run of the k range through LDS stages of its own, and the epilogue adds the groups'
+// accumulators in group order.  NST operand stages in LDS.  Per k-tile t: k-steps
 // 0..KS-2 read the next step's fragments and issue this step's MFMAs; then the wait for tile
 // t+1's fill and the workgroup barrier, after which tile t's stage takes tile t+NST and tile
 // t+1's first fragments are read while the last k-step's MFMAs run.  Fills are issued NST-1
 // tiles ahead; fragment reads are explicit (see lds_read16), so no read waits for a fill it
 // does not need.  OCC workgroups share a CU: with two, one workgroup's epilogue (GELU math,
 // output stores) overlaps the other's MFMAs.
-template <int BM, int BN, int NST, int OCC, bool AK, bool BK, int EPI, typename T, typename Ta>
-__global__ __launch_bounds__(256, OCC) void gemm_mfma_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ Bm,
+template <int BM, int BN, int WM, int WN, int KG, int NST, int OCC, bool AK, bool BK, int EPI, typename T, typename Ta>
+__global__ __launch_bounds__(64 * WM * WN * KG, OCC) void gemm_mfma_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ Bm,
                                                            int M, int N, int Kd, int lda, int ldb, uint32_t a_bytes,
                                                            uint32_t b_bytes, int k_per_split, int tiles_m, int tiles_n,
                                                            EpiArgs ep) {
-  constexpr int MI = BM / 64, NJ = BN / 64;
-  static_assert(BM == 64 || BM == 128 || BM == 256, "tile height");
-  static_assert(BN == 128 || BN == 256, "tile width");
+  constexpr int NW = WM * WN, NT = 64 * NW * KG;
+  constexpr int MI = BM / (32 * WM), NJ = BN / (32 * WN);
+  static_assert(MI * 32 * WM == BM && NJ * 32 * WN == BN && MI > 0 && NJ > 0, "tile of whole MFMA tiles per wave");
+  static_assert(BM / 8 % NW == 0 && BN / 8 % NW == 0, "a group's waves share the fills evenly");
+  static_assert(EPI != EPI_DW || KG == 1, "bias-gradient sums assume one group");
+  static_assert(EPI != EPI_DO || BN >= 64, "a head's columns lie in one tile");
   static_assert(NST >= 2 && NST <= 4, "stages");
   constexpr int STAGE = (BM + BN) * GK;   // bf16 elements: A tile, then B tile
   constexpr int SB = STAGE * 2;           // bytes of a stage
-  constexpr int LPT = (BM + BN) / 32;     // fill instructions per thread per tile
+  constexpr int LPT = (BM + BN) / 8 / NW;   // fill instructions per thread per tile
   static_assert((NST - 1) * LPT < 64, "loads in flight exceed the vmcnt range");
   using FA = FragAddr<BM, AK, MI>;
   using FB = FragAddr<BN, BK, NJ>;
   constexpr int RPK = FA::kReads + FB::kReads;   // LDS reads per k-step
   static_assert(RPK < 16, "reads per k-step exceed the lgkmcnt range");
-  __shared__ __attribute__((aligned(1024))) bf16_t smem[NST * STAGE];
+  __shared__ __attribute__((aligned(1024))) bf16_t smem[KG * NST * STAGE];
 
-  const int lane = threadIdx.x & 63, wid = wave_index();
-  const int wm = wid >> 1, wn = wid & 1, h = lane >> 5;
+  const int lane = threadIdx.x & 63, wave = wave_index();
+  const int grp = wave / NW, wid = wave % NW;
+  const int wm = wid / WN, wn = wid % WN, h = lane >> 5;
   int tm, tn, split;
   tile_coords(blockIdx.x, gridDim.x, tiles_m, tiles_n, tm, tn, split);
   const int m0 = tm * BM, n0 = tn * BN;
-  const int kbeg = split * k_per_split;
+  int kbeg = split * k_per_split;
   const int kend = min(Kd, kbeg + k_per_split);
-  const int ntile = kbeg < kend ? (kend - kbeg + GK - 1) / GK : 0;
+  int ntile = kbeg < kend ? (kend - kbeg + GK - 1) / GK : 0;
+  int nmine = ntile;   // this group's k-tiles; every group runs ntile, the missing ones on zeros
+  if constexpr (KG > 1) {
+    const int all = ntile;
+    ntile = (all + KG - 1) / KG;
+    kbeg += grp * ntile * GK;
+    nmine = min(ntile, all - grp * ntile);
+  }
   const __amdgpu_buffer_rsrc_t ra = make_rsrc(A, a_bytes);
   const __amdgpu_buffer_rsrc_t rb = make_rsrc(Bm, b_bytes);
 
@@ -321,22 +333,22 @@ __global__ __launch_bounds__(256, OCC) void gemm_mfma_kernel(const bf16_t* __res
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  TileFill<BM, AK> fla;
-  TileFill<BN, BK> flb;
+  TileFill<BM, AK, NW> fla;
+  TileFill<BN, BK, NW> flb;
   fla.init(m0, lda, lane, wid);
   flb.init(n0, ldb, lane, wid);
   auto fill = [&](int t, int s) {
-    bf16_t* st = smem + s * STAGE;
+    bf16_t* st = smem + (grp * NST + s) * STAGE;
     const uint32_t k0 = (uint32_t)(kbeg + t * GK);
-    const bool valid = t < ntile;
-    fill_issue<BM / 32>(fla.off, ra, st, wid, valid ? k0 * (AK ? 2u : 2u * (uint32_t)lda) : 0x80000000u);
-    fill_issue<BN / 32>(flb.off, rb, st + BM * GK, wid, valid ? k0 * (BK ? 2u : 2u * (uint32_t)ldb) : 0x80000000u);
+    const bool valid = t < nmine;
+    fill_issue<BM / 8 / NW>(fla.off, ra, st, wid, valid ? k0 * (AK ? 2u : 2u * (uint32_t)lda) : 0x80000000u);
+    fill_issue<BN / 8 / NW>(flb.off, rb, st + BM * GK, wid, valid ? k0 * (BK ? 2u : 2u * (uint32_t)ldb) : 0x80000000u);
   };
-  const uint32_t sbase = lds_addr(smem);
+  const uint32_t sbase = lds_addr(smem) + (uint32_t)(grp * NST * SB);
   FA fad;
   FB fbd;
-  fad.init(sbase, wm * (BM / 2), lane);
-  fbd.init(sbase + BM * GK * 2, wn * (BN / 2), lane);
+  fad.init(sbase, wm * (BM / WM), lane);
+  fbd.init(sbase + BM * GK * 2, wn * (BN / WN), lane);
   RawFrag<AK> fa[2][MI];
   RawFrag<BK> fb[2][NJ];
   bf16x8 ua[MI], ub[NJ];   // settled operands of the k-step being multiplied
@@ -363,18 +375,18 @@ __global__ __launch_bounds__(256, OCC) void gemm_mfma_kernel(const bf16_t* __res
 
   // EPI_DW bias gradient: row sums of A (r-major there: k-rows of BM values).  The tile row's
   // tiles_n workgroups share the work: workgroup tn sums the k-tiles t with t % tiles_n == tn.
-  // Thread: chunk position cp of k-rows kg, kg + KG, ...; eight running sums.
-  constexpr int CPR = BM / 8, KG = 256 / CPR;
+  // Thread: chunk position cp of k-rows kg, kg + DBG, ...; eight running sums.
+  constexpr int CPR = BM / 8, DBG = 256 / CPR;
   const bool want_db = EPI == EPI_DW && ep.db_out != nullptr;
   float dbv[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   const uint32_t db_addr = sbase + (uint32_t)(((threadIdx.x / CPR) * BM + (threadIdx.x % CPR) * 8) * 2);
   auto db_sum = [&](auto sidx) {
     constexpr int S = decltype(sidx)::value;
-    i32x4 w[64 / KG];
-    static_for<64 / KG>([&](auto j) { w[j.value] = rd16<S * SB + j.value * KG * BM * 2>(db_addr); });
+    i32x4 w[64 / DBG];
+    static_for<64 / DBG>([&](auto j) { w[j.value] = rd16<S * SB + j.value * DBG * BM * 2>(db_addr); });
     lgkm_wait<0>();
 #pragma unroll
-    for (int j = 0; j < 64 / KG; ++j) {
+    for (int j = 0; j < 64 / DBG; ++j) {
       pin(w[j]);
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
@@ -434,8 +446,8 @@ __global__ __launch_bounds__(256, OCC) void gemm_mfma_kernel(const bf16_t* __res
 
   if constexpr (EPI == EPI_DW) {
     if (want_db) {
-      // combine the KG partial sums of each row through LDS, in k-group order
-      float* red = reinterpret_cast<float*>(smem);   // [KG][BM]
+      // combine the DBG partial sums of each row through LDS, in k-group order
+      float* red = reinterpret_cast<float*>(smem);   // [DBG][BM]
       const int cp = threadIdx.x % CPR, kg = threadIdx.x / CPR;
       const int lc = cp ^ rswz<BM>(kg);   // logical chunk this thread summed
 #pragma unroll
@@ -443,7 +455,7 @@ __global__ __launch_bounds__(256, OCC) void gemm_mfma_kernel(const bf16_t* __res
       __syncthreads();
       if ((int)threadIdx.x < BM) {
         float sum = 0.f;
-        for (int g = 0; g < KG; ++g) sum += red[g * BM + threadIdx.x];
+        for (int g = 0; g < DBG; ++g) sum += red[g * BM + threadIdx.x];
         const int row = m0 + threadIdx.x;
         const int nparts = gridDim.x / (tiles_m * tiles_n) * tiles_n;
         if (row < M) {
@@ -455,35 +467,38 @@ __global__ __launch_bounds__(256, OCC) void gemm_mfma_kernel(const bf16_t* __res
     }
   }
 
-  // epilogue in MI passes of 64 rows: pass p stages i-block p of both wave rows (every wave
+  // epilogue in MI passes of PR rows: pass p stages i-block p of all wave rows (every wave
   // writes; register r of a 32 x 32 MFMA tile holds row 8 (r/4) + 4 h + r%4, column lane%32)
-  // as fp32 in LDS, then each thread finishes NB 4-column chunks.  The epilogue's global inputs
-  // (residual, GELU pre-activation, O) of every pass are loaded before the first pass and the
-  // bias once, so no pass waits on a global load it issued itself.
+  // as fp32 in LDS, one plane per group, then each thread finishes NB 4-column chunks.  The
+  // epilogue's global inputs (residual, GELU pre-activation, O) of every pass are loaded before
+  // the first pass and the bias once, so no pass waits on a global load it issued itself.
   if constexpr (EPI == EPI_DW)
     if (gridDim.x > (unsigned)(tiles_m * tiles_n)) ep.out_f32 = ep.part + (size_t)split * ep.split_stride;
-  constexpr int PR = 64;
+  float* stg = reinterpret_cast<float*>(smem);
+  constexpr int PR = 32 * WM;
   constexpr int EPI_LD = BN + 8;   // fp32 row stride: the two halves of a wave hit disjoint banks
   constexpr int CPRo = BN / 4;     // 4-column chunks per row
-  constexpr int NB = PR * CPRo / 256;
-  static_assert(256 % CPRo == 0, "a thread's chunks share their columns");
+  constexpr int NB = (PR * CPRo + NT - 1) / NT;
+  static_assert(NT % CPRo == 0, "a thread's chunks share their columns");
+  static_assert(NB * NT == PR * CPRo || NB == 1, "whole chunk rounds");
   static_assert(PR * EPI_LD * 4 <= NST * SB, "epilogue staging exceeds the stages");
-  float* stg = reinterpret_cast<float*>(smem);
-  // chunk q of pass p: staging row lr = c / CPRo (c = tid + 256 q), columns c4 .. c4 + 3
+  const bool active = PR * CPRo >= NT || (int)threadIdx.x < PR * CPRo;
+  // chunk q of pass p: staging row lr = c / CPRo (c = tid + NT q), columns c4 .. c4 + 3
   auto chunk_row = [&](int p, int q) {
-    const int lr = (threadIdx.x + 256 * q) / CPRo;
-    return m0 + (lr >> 5) * (BM / 2) + p * 32 + (lr & 31);
+    const int lr = (threadIdx.x + NT * q) / CPRo;
+    return m0 + (lr >> 5) * (BM / WM) + p * 32 + (lr & 31);
   };
   const int c4 = (threadIdx.x % CPRo) * 4;
   const int n = n0 + c4;
-  const f32x4 bias = n < N ? epi_bias<EPI>(ep, n) : f32x4{0.f, 0.f, 0.f, 0.f};
+  const bool col_ok = active && n < N;
+  const f32x4 bias = col_ok ? epi_bias<EPI>(ep, n) : f32x4{0.f, 0.f, 0.f, 0.f};
   EpiIn in[MI][NB];
 #pragma unroll
   for (int p = 0; p < MI; ++p)
 #pragma unroll
     for (int q = 0; q < NB; ++q) {
       const int m = chunk_row(p, q);
-      if (m < M && n < N) epi_load<EPI>(ep, m, n, in[p][q]);
+      if (m < M && col_ok) epi_load<EPI>(ep, m, n, in[p][q]);
     }
 #pragma unroll
   for (int p = 0; p < MI; ++p) {
@@ -492,20 +507,25 @@ __global__ __launch_bounds__(256, OCC) void gemm_mfma_kernel(const bf16_t* __res
     for (int j = 0; j < NJ; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r)
-        stg[(wm * 32 + 8 * (r >> 2) + 4 * h + (r & 3)) * EPI_LD + wn * (BN / 2) + j * 32 + (lane & 31)] = acc[p][j][r];
+        stg[(grp * PR + wm * 32 + 8 * (r >> 2) + 4 * h + (r & 3)) * EPI_LD + wn * (BN / WN) + j * 32 + (lane & 31)] =
+            acc[p][j][r];
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < NB; ++q) {
-      const int lr = (threadIdx.x + 256 * q) / CPRo;
+      const int lr = (threadIdx.x + NT * q) / CPRo;
       const int m = chunk_row(p, q);
       float part = 0.f;
-      if (m < M && n < N)
-        part = epi_store<EPI>(ep, m, n, *reinterpret_cast<const f32x4*>(stg + lr * EPI_LD + c4), in[p][q], bias);
+      if (m < M && col_ok) {
+        f32x4 v = *reinterpret_cast<const f32x4*>(stg + lr * EPI_LD + c4);
+#pragma unroll
+        for (int g = 1; g < KG; ++g) v += *reinterpret_cast<const f32x4*>(stg + (g * PR + lr) * EPI_LD + c4);
+        part = epi_store<EPI>(ep, m, n, v, in[p][q], bias);
+      }
       if constexpr (EPI == EPI_DO) {
         // the 16 lanes (tid % 16) of one head's 64 columns: butterfly within the group
 #pragma unroll
         for (int o = 8; o >= 1; o >>= 1) part += __shfl_xor(part, o, 64);
-        if ((threadIdx.x & 15) == 0 && m < M && n < N)
+        if ((threadIdx.x & 15) == 0 && m < M && col_ok)
           ep.delta[((size_t)(m / ep.S) * ep.H + (n >> 6)) * ep.S + (m % ep.S)] = part;
       }
     }
@@ -675,21 +695,37 @@ __global__ __launch_bounds__(256) void gemm_simple_kernel(const TA* __restrict__
 
 // ============================================================================ dispatch
 
-// Tile shapes of the MFMA kernel, with the stage count that fits the 160 KB of LDS.
-enum TileShape { T256x256 = 0, T256x128 = 1, T128x256 = 2, T128x128 = 3, T64x128 = 4, T128x128x2 = 5 };
+// Tile shapes of the MFMA kernel: rows x columns, k groups, stages and workgroups per CU.
+enum TileShape { T128x128x2, T128x128, T64x128, T64x64g2, T32x64g4, T32x32g8 };
+struct ShapeInfo {
+  int bm, bn, occ;
+};
+static ShapeInfo shape_info(int s) {
+  switch (s) {
+    case T128x128x2: return {128, 128, 2};
+    case T128x128: return {128, 128, 1};
+    case T64x128: return {64, 128, 1};
+    case T32x64g4: return {32, 64, 1};
+    case T32x32g8: return {32, 32, 1};
+    default: return {64, 64, 1};
+  }
+}
 
-template <int BM, int BN, int NST, int OCC, int EPI, typename T, typename Ta>
+template <int BM, int BN, int WM, int WN, int KG, int NST, int OCC, int EPI, typename T, typename Ta>
 static hipError_t run_mfma_tile(const GemmDesc& g, const EpiArgs& ep, int splits, int kps, hipStream_t st) {
   const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
   const dim3 grid((unsigned)(tiles_m * tiles_n * splits));
 #define SR_GEMM_L(AK, BK)                                                                                        \
-  SR_LAUNCH((gemm_mfma_kernel<BM, BN, NST, OCC, AK, BK, EPI, T, Ta>), grid, dim3(256), 0, st,            \
-                     (const bf16_t*)g.A, (const bf16_t*)g.B, g.M, g.N, g.K, (int)g.lda, (int)g.ldb,               \
-                     (uint32_t)g.a_bytes, (uint32_t)g.b_bytes, kps, tiles_m, tiles_n, ep)
-  if (g.a_kmajor && g.b_kmajor) SR_GEMM_L(true, true);
-  else if (g.a_kmajor && !g.b_kmajor) SR_GEMM_L(true, false);
-  else if (!g.a_kmajor && !g.b_kmajor) SR_GEMM_L(false, false);
-  else SR_GEMM_L(false, true);
+  SR_LAUNCH((gemm_mfma_kernel<BM, BN, WM, WN, KG, NST, OCC, AK, BK, EPI, T, Ta>), grid, dim3(64 * WM * WN * KG), \
+            0, st, (const bf16_t*)g.A, (const bf16_t*)g.B, g.M, g.N, g.K, (int)g.lda, (int)g.ldb,                 \
+            (uint32_t)g.a_bytes, (uint32_t)g.b_bytes, kps, tiles_m, tiles_n, ep)
+  if constexpr (EPI == EPI_DW) {
+    SR_GEMM_L(false, false);
+  } else {
+    if (!g.a_kmajor) return hipErrorInvalidValue;   // only the weight gradients read A token-major
+    if (g.b_kmajor) SR_GEMM_L(true, true);
+    else SR_GEMM_L(true, false);
+  }
 #undef SR_GEMM_L
   return hipGetLastError();
 }
@@ -697,28 +733,43 @@ static hipError_t run_mfma_tile(const GemmDesc& g, const EpiArgs& ep, int splits
 template <int EPI, typename T, typename Ta>
 static hipError_t run_shape(int shape, const GemmDesc& g, const EpiArgs& ep, int splits, int kps, hipStream_t st) {
   switch (shape) {
-    case T256x128: return run_mfma_tile<256, 128, 3, 1, EPI, T, Ta>(g, ep, splits, kps, st);
-    case T128x256: return run_mfma_tile<128, 256, 3, 1, EPI, T, Ta>(g, ep, splits, kps, st);
-    case T128x128: return run_mfma_tile<128, 128, 4, 1, EPI, T, Ta>(g, ep, splits, kps, st);
-    case T128x128x2: return run_mfma_tile<128, 128, 2, 2, EPI, T, Ta>(g, ep, splits, kps, st);
-    default: return run_mfma_tile<64, 128, 4, 1, EPI, T, Ta>(g, ep, splits, kps, st);
+    case T128x128: return run_mfma_tile<128, 128, 2, 2, 1, 4, 1, EPI, T, Ta>(g, ep, splits, kps, st);
+    case T128x128x2: return run_mfma_tile<128, 128, 2, 2, 1, 2, 2, EPI, T, Ta>(g, ep, splits, kps, st);
+    case T64x128: return run_mfma_tile<64, 128, 2, 2, 1, 4, 1, EPI, T, Ta>(g, ep, splits, kps, st);
+    default: break;
   }
+  if constexpr (EPI != EPI_DW) {
+    switch (shape) {
+      case T64x64g2: return run_mfma_tile<64, 64, 2, 2, 2, 4, 1, EPI, T, Ta>(g, ep, splits, kps, st);
+      case T32x64g4: return run_mfma_tile<32, 64, 1, 2, 4, 3, 1, EPI, T, Ta>(g, ep, splits, kps, st);
+      default: break;
+    }
+    if constexpr (EPI != EPI_DO)
+      if (shape == T32x32g8) return run_mfma_tile<32, 32, 1, 1, 8, 2, 1, EPI, T, Ta>(g, ep, splits, kps, st);
+  }
+  return hipErrorInvalidValue;
 }
 
-static int shape_bm(int s) { return s == T256x256 || s == T256x128 ? 256 : s == T64x128 ? 64 : 128; }
-static int shape_occ(int s) { return s == T128x128x2 ? 2 : 1; }
-static int shape_bn(int s) { return s == T256x256 || s == T128x256 ? 256 : 128; }
+static long tile_count(int s, int M, int N) {
+  const ShapeInfo si = shape_info(s);
+  return (long)((M + si.bm - 1) / si.bm) * ((N + si.bn - 1) / si.bn);
+}
 
-// Tile shape by the number of 128 x 128 output tiles (measured on the block's GEMMs at 4050
-// tokens on MI355X): many tiles -> two 128 x 128 workgroups per CU (one's epilogue overlaps the
-// other's MFMAs); about one per CU -> one workgroup with a four-stage pipeline; fewer -> 64 x 128
-// tiles so that the grid still covers the CUs.  The 256 x 128 shapes measured slower throughout
-// and stay available to the benchmarks only.
-static int pick_shape(int M, int N, int splits) {
-  const long tiles = (long)((M + 127) / 128) * ((N + 127) / 128) * splits;
-  if (tiles >= 384) return T128x128x2;
-  if (tiles >= 192) return T128x128;
-  return T64x128;
+// Products of the forward and of dX: the smallest tile whose grid is one round of workgroups on
+// the 256 CUs.  With fewer tiles than CUs a launch lasts as long as one workgroup, so a smaller
+// tile with its k range shared by more waves is faster; past one round the larger tile is, as it
+// fetches fewer operand bytes per output.  Measured on MI355X (us; M x N x K):
+//   128 x 1024 x 4096: 64 x 128 20.0, 64 x 64 with two groups 13.4, 32 x 64 with four 11.2,
+//   32 x 32 with eight (128 tiles) 10.2;  128 x 3072 x 1024: 8.0, 6.4, 6.0 (192 tiles), 8.5 (384)
+//   512 x 1024 x 4096: 20.5, 14.4, 12.1 (256), 19.0 (512);  1024 x 1024 x 4096: 21.2, 15.7 (256),
+//   22.1 (512);  2048 x 1024 x 4096: 24.8 (256), 29.9 (512), 128 x 128 34.6 (128)
+//   1024 x 3072 x 1024: 64 x 128 14.8 (384), 128 x 128 13.0 (192)
+// Past one round of 128 x 128 tiles, two workgroups per CU: one's epilogue overlaps the other's
+// MFMAs (2048 x 3072 x 1024: 24.8 -> 21.5; 4050 x 4096 x 1024 with GELU: 72 -> 57).
+static int pick_shape(int M, int N, bool whole_heads) {
+  for (int s : {T32x32g8, T32x64g4, T64x64g2, T64x128, T128x128})
+    if (!(s == T32x32g8 && whole_heads) && tile_count(s, M, N) <= 256) return s;
+  return T128x128x2;
 }
 
 #ifdef SR_GEMM_FORCE_SHAPE
@@ -727,13 +778,11 @@ int g_force_shape = -1;   // standalone benchmarks: >= 0 overrides the choice
 
 template <int EPI, typename T, typename Ta>
 static hipError_t run_mfma(const GemmDesc& g, const EpiArgs& ep, hipStream_t st) {
-  const int splits = g.splits > 1 ? g.splits : 1;
-  const int kps = splits > 1 ? g.k_per_split : g.K;
-  int shape = pick_shape(g.M, g.N, splits);
+  int shape = pick_shape(g.M, g.N, EPI == EPI_DO);
 #ifdef SR_GEMM_FORCE_SHAPE
   if (g_force_shape >= 0) shape = g_force_shape;
 #endif
-  return run_shape<EPI, T, Ta>(shape, g, ep, splits, kps, st);
+  return run_shape<EPI, T, Ta>(shape, g, ep, 1, g.K, st);
 }
 
 // Weight gradient (EPI_DW; reduction over tokens, both operands r-major): shape and split-K
@@ -744,13 +793,15 @@ struct DwPlan {
 };
 static DwPlan dw_plan(int M, int N, int K) {
   DwPlan p;
-  p.shape = pick_shape(M, N, 1);
+  const long t = tile_count(T128x128, M, N);
+  p.shape = t >= 384 ? T128x128x2 : t >= 192 ? T128x128 : T64x128;
 #ifdef SR_GEMM_FORCE_SHAPE
   if (g_force_shape >= 0) p.shape = g_force_shape;
 #endif
-  const int bm = shape_bm(p.shape), bn = shape_bn(p.shape);
+  const ShapeInfo si = shape_info(p.shape);
+  const int bm = si.bm, bn = si.bn;
   const long tiles = (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn);
-  int sp = (int)(256 * shape_occ(p.shape) / tiles);   // one round of workgroups at most
+  int sp = (int)(256 * si.occ / tiles);   // one round of workgroups at most
   sp = std::min(sp, std::max(1, K / 512));
   sp = std::max(1, std::min(sp, 8));
   p.kps = ((K + sp - 1) / sp + GK - 1) / GK * GK;

@@ -64,7 +64,6 @@ struct GemmDesc {
   long long lda = 0, ldb = 0;
   size_t a_bytes = 0, b_bytes = 0;  // exact sizes of the operands (bounds of the buffer loads)
   bool a_kmajor = true, b_kmajor = true;
-  int splits = 1, k_per_split = 0;
   bool use_mfma = false;
   int dtype = kBF16;          // storage type (bias / residual output)
   int a_type = kBF16, b_type = kBF16;
