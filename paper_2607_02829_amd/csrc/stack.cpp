@@ -352,7 +352,11 @@ hipError_t stack_bwd(const Dims& d, const sr_block_params* p, const void* cond, 
   hipStream_t side = nullptr;
   BwdEvents* ev = nullptr;
   bool pending[kSlots] = {};   // recorded and not yet waited on
-  const bool serial = profiling_all();
+  // The forks and joins cost the host about 70 us per block, so a small call goes to the caller's stream
+  // alone.  Two blocks forward and backward, us on two streams and on one at tokens x D:
+  // 32 x 128 382, 219; 256 x 256 339, 247; 512 x 256 350, 293; 128 x 1024 345, 335; above, what overlaps is
+  // worth more (256 x 1024 346, 373; 1024 x 512 388, 404).
+  const bool serial = profiling_all() || (size_t)M * D <= (size_t)1 << 17;
   // Fork points: the main-stream kernels right before a fork carry the fork event themselves
   // (bound at launch, see LaunchHook), and the fork waits on the event the last of them carries,
   // provided no kernel was launched in between; otherwise it records the event on st.  Not while
