@@ -112,7 +112,6 @@ GemmDesc desc(const EdmDims& d, const void* A, bool ak, long long lda, size_t ab
   g.a_kmajor = ak; g.b_kmajor = bk;
   g.use_mfma = d.dtype == kBF16;
   g.dtype = d.dtype;
-  g.a_type = d.dtype; g.b_type = d.dtype;
   return g;
 }
 
@@ -401,13 +400,9 @@ hipError_t edm_bwd(const EdmDims& d, const sr_edm_block_params* p, const void* e
     SR_TRY(reduce_ln(g.ln2_w, g.ln2_b));
     // ---------------------------------------------------------------- gated cross-attention
     SR_TRY(join(kOc));   // dc may still be read by the previous block's dW_oc
-    {   // dc = dh2 g (storage copy); dlogit = sum_s dh2 c_out, then times g (1 - g)
-      ProfScope ps("convert", 0, (double)M * D * (d.elt + 4), st);
-      SR_TRY(launch_convert(kF32, sc.g_res2, d.dtype, sc.dc, (size_t)M * D, s.mod + 2 * D, 6 * D, S, D, nullptr, st));
-    }
-    SR_TRY(fork_point([&]() -> hipError_t {
-      ProfScope ps("colsum", 0, (double)M * D * (4 + d.elt), st);
-      SR_TRY(launch_colsum(kF32, sc.g_res2, d.dtype, s.c_out, nullptr, 0, B, S, D, sc.part, st));
+    SR_TRY(fork_point([&]() -> hipError_t {   // dc = dh2 g (storage copy); dlogit = sum_s dh2 c_out, then times g (1 - g)
+      ProfScope ps("colsum", 0, (double)M * D * (4 + 2 * d.elt), st);
+      SR_TRY(launch_gate_bwd(d.dtype, sc.g_res2, s.c_out, s.mod + 2 * D, 6 * D, B, S, D, sc.dc, sc.part, st));
       SR_TRY(launch_reduce_cols(sc.part, colsum_chunks(S), B, 0, D, D, sc.dmod + 2 * D, nullptr, 6 * D, st));
       return launch_sigmoid_grad(sc.dmod + 2 * D, s.mod + 2 * D, B, D, 6 * D, st);
     }));
@@ -481,18 +476,10 @@ hipError_t edm_bwd(const EdmDims& d, const sr_edm_block_params* p, const void* e
     {   // parameters of the modulation and the noise embedding's gradient
       ProfScope ps("mod", 0, 0, st);
       if (g.w_film) {   // dW_film = dfilm^T e (dfilm = dmod[:, 0:2D])
-        GemmDesc gd = desc(d, sc.dmod, false, 6 * D, (size_t)B * 6 * D * 4, e_sig, false, D, (size_t)B * D * d.elt,
-                           2 * D, D, B);
-        gd.use_mfma = false; gd.a_type = kF32;
-        EpiArgs ep; ep.out_f32 = g.w_film; ep.ldo = D;
-        SR_TRY(launch_gemm(gd, EPI_F32, ep, st));
+        SR_TRY(launch_outer(d.dtype, sc.dmod, 6 * D, e_sig, B, 2 * D, D, g.w_film, st));
       }
       if (g.w_g) {      // dW_g = dlogit^T e (dlogit = dmod[:, 2D:3D])
-        GemmDesc gd = desc(d, sc.dmod + 2 * D, false, 6 * D, (size_t)B * 6 * D * 4 - 2 * D * 4, e_sig, false, D,
-                           (size_t)B * D * d.elt, D, D, B);
-        gd.use_mfma = false; gd.a_type = kF32;
-        EpiArgs ep; ep.out_f32 = g.w_g; ep.ldo = D;
-        SR_TRY(launch_gemm(gd, EPI_F32, ep, st));
+        SR_TRY(launch_outer(d.dtype, sc.dmod + 2 * D, 6 * D, e_sig, B, D, D, g.w_g, st));
       }
       SR_TRY(launch_sum_samples(sc.dmod, B, 2 * D, 6 * D, g.b_film, st));
       SR_TRY(launch_sum_samples(sc.dmod + 2 * D, B, D, 6 * D, g.b_g, st));

@@ -96,8 +96,6 @@ SR_DEV void epilogue(const EpiArgs& e, int m, int n, float v) {
     e.out_f32[o] = v;
   } else if constexpr (EPI == EPI_F32_ACC) {
     e.out_f32[o] += v;
-  } else if constexpr (EPI == EPI_BIAS_F32) {
-    e.out_f32[o] = v + to_f32<T>(((const T*)e.bias)[n]);
   }
 }
 

@@ -15,8 +15,8 @@
 // Global loads go through buffer resources, so rows past the end of an operand
 // read as zero: ragged token counts need no predicates in the main loop.
 //
-// gemm_simple: any element type, generic strides, fp32 FMA; used for the tiny adaLN and FiLM
-// modulation products.  The fp32 storage mode's GEMMs are in gemm_f32.hip.
+// The fp32 storage mode's GEMMs are in gemm_f32.hip, the products of the adaLN and FiLM
+// conditioning in gemv.hip.
 //
 // Epilogues (per element, fp32 value v = accumulator):
 //   EPI_BIAS_ACT  out_act = Ta(v + bias)                           (QKV)
@@ -27,7 +27,6 @@
 //   EPI_ACT       out_act = Ta(v)                                   (O-proj dX)
 //   EPI_F32       out_f32[split] = v                                (dX for LN, dW partials)
 //   EPI_F32_ACC   out_f32 += v                                      (dcond over blocks)
-//   EPI_BIAS_F32  out_f32 = v + bias                                (adaLN modulation vectors)
 //   EPI_DO        out_act = Ta(v); delta = per-head row sums of Ta(v) * O (attention backward)
 //   EPI_DW        dW = v, db = row sums of A (weight and bias gradients); with split-K each
 //                 split writes a partial plane and reduce_splits_kernel sums the planes in
@@ -70,7 +69,7 @@ SR_DEV f32x4 unpack4(i32x2 w) {
 }
 
 constexpr bool epi_has_bias(int epi) {
-  return epi == EPI_BIAS_ACT || epi == EPI_RESID || epi == EPI_GELU || epi == EPI_BIAS_F32;
+  return epi == EPI_BIAS_ACT || epi == EPI_RESID || epi == EPI_GELU;
 }
 
 // Bias of the four columns n..n+3 (zero for epilogues without one).
@@ -135,8 +134,6 @@ SR_DEV float epi_store(const EpiArgs& e, int m, int n, f32x4 v, const EpiIn& in,
     *reinterpret_cast<f32x4*>(e.out_f32 + o) = v;
   } else if constexpr (EPI == EPI_F32_ACC) {
     *reinterpret_cast<f32x4*>(e.out_f32 + o) = in.resid + v;
-  } else if constexpr (EPI == EPI_BIAS_F32) {
-    *reinterpret_cast<f32x4*>(e.out_f32 + o) = v + b;
   } else if constexpr (EPI == EPI_DW) {
     *reinterpret_cast<f32x4*>(e.out_f32 + o) = v;   // the split's partial plane when split
   } else if constexpr (EPI == EPI_DO) {
@@ -643,56 +640,6 @@ static hipError_t launch_reduce(const float* part, int splits, size_t n, float* 
   return hipGetLastError();
 }
 
-// ============================================================================ generic kernel
-
-template <typename TA, typename TB, int EPI, typename T, typename Ta>
-__global__ __launch_bounds__(256) void gemm_simple_kernel(const TA* __restrict__ A, const TB* __restrict__ Bm, int M,
-                                                          int N, int Kd, long long a_sm, long long a_sk,
-                                                          long long b_sn, long long b_sk, EpiArgs ep) {
-  __shared__ float As[16][65];
-  __shared__ float Bs[16][65];
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  float acc[4][4] = {};
-  const bool do_db = EPI == EPI_DW && ep.db_out != nullptr && blockIdx.x == 0;
-  float dbacc = 0.f;
-  for (int k0 = 0; k0 < Kd; k0 += 16) {
-    for (int t = threadIdx.x; t < 64 * 16; t += 256) {
-      const int kk = t >> 6, r = t & 63;
-      const int m = m0 + r, n = n0 + r, k = k0 + kk;
-      As[kk][r] = (m < M && k < Kd) ? to_f32<TA>(A[m * a_sm + k * a_sk]) : 0.f;
-      Bs[kk][r] = (n < N && k < Kd) ? to_f32<TB>(Bm[n * b_sn + k * b_sk]) : 0.f;
-    }
-    __syncthreads();
-    if (do_db && threadIdx.x < 64)
-      for (int kk = 0; kk < 16; ++kk) dbacc += As[kk][threadIdx.x];
-#pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-  if (do_db && threadIdx.x < 64 && m0 + (int)threadIdx.x < M) ep.db_out[m0 + threadIdx.x] = dbacc;
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int m = m0 + ty * 4 + i, n = n0 + tx * 4 + j;
-      if (m < M && n < N) {
-        if constexpr (EPI == EPI_DW) ep.out_f32[(size_t)m * ep.ldo + n] = acc[i][j];
-        else epilogue<EPI, T, Ta>(ep, m, n, acc[i][j]);
-      }
-    }
-}
-
 // ============================================================================ dispatch
 
 // Tile shapes of the MFMA kernel: rows x columns, k groups, stages and workgroups per CU.
@@ -811,28 +758,10 @@ static DwPlan dw_plan(int M, int N, int K) {
   return p;
 }
 
-template <int EPI, typename T, typename Ta, typename TA, typename TB>
-static hipError_t run_simple(const GemmDesc& g, const EpiArgs& ep, hipStream_t st) {
-  dim3 grid((g.N + 63) / 64, (g.M + 63) / 64, 1);
-  const long long a_sm = g.a_kmajor ? g.lda : 1, a_sk = g.a_kmajor ? 1 : g.lda;
-  const long long b_sn = g.b_kmajor ? g.ldb : 1, b_sk = g.b_kmajor ? 1 : g.ldb;
-  SR_LAUNCH((gemm_simple_kernel<TA, TB, EPI, T, Ta>), grid, dim3(256), 0, st, (const TA*)g.A,
-                     (const TB*)g.B, g.M, g.N, g.K, a_sm, a_sk, b_sn, b_sk, ep);
-  return hipGetLastError();
-}
-
 template <int EPI>
 static hipError_t dispatch(const GemmDesc& g, const EpiArgs& ep, hipStream_t st) {
   if (g.use_mfma) return run_mfma<EPI, bf16_t, bf16_t>(g, ep, st);
-  // simple path: element types of A and B, T/Ta = storage / activation type
-  if (g.dtype == kBF16) {
-    if (g.a_type == kBF16 && g.b_type == kBF16) return run_simple<EPI, bf16_t, bf16_t, bf16_t, bf16_t>(g, ep, st);
-    if (g.a_type == kF32 && g.b_type == kBF16) return run_simple<EPI, bf16_t, bf16_t, float, bf16_t>(g, ep, st);
-    if (g.a_type == kBF16 && g.b_type == kF32) return run_simple<EPI, bf16_t, bf16_t, bf16_t, float>(g, ep, st);
-    return run_simple<EPI, bf16_t, bf16_t, float, float>(g, ep, st);
-  }
-  if (gemm_f32_takes(g, EPI)) return launch_gemm_f32(g, EPI, ep, st);
-  return run_simple<EPI, float, float, float, float>(g, ep, st);
+  return gemm_f32_takes(g, EPI) ? launch_gemm_f32(g, EPI, ep, st) : hipErrorInvalidValue;
 }
 
 hipError_t launch_gemm(const GemmDesc& g, int epi, const EpiArgs& ep, hipStream_t st) {
@@ -844,8 +773,6 @@ hipError_t launch_gemm(const GemmDesc& g, int epi, const EpiArgs& ep, hipStream_
     case EPI_ACT: return dispatch<EPI_ACT>(g, ep, st);
     case EPI_F32: return dispatch<EPI_F32>(g, ep, st);
     case EPI_F32_ACC: return dispatch<EPI_F32_ACC>(g, ep, st);
-    case EPI_BIAS_F32: return dispatch<EPI_BIAS_F32>(g, ep, st);
-    case EPI_DW: return g.use_mfma ? hipErrorInvalidValue : dispatch<EPI_DW>(g, ep, st);   // launch_weight_grad
     case EPI_DO: return g.use_mfma ? run_mfma<EPI_DO, bf16_t, bf16_t>(g, ep, st) : hipErrorInvalidValue;
   }
   return hipErrorInvalidValue;
@@ -904,7 +831,7 @@ hipError_t launch_weight_grad(const GemmDesc& g, float* dw, float* db, float* pa
   if (!g.use_mfma) {
     ep.out_f32 = dw;
     ep.db_out = db;
-    return dispatch<EPI_DW>(g, ep, st);
+    return gemm_f32_takes(g, EPI_DW) ? launch_gemm_f32(g, EPI_DW, ep, st) : hipErrorInvalidValue;
   }
   const DwPlan p = dw_plan(g.M, g.N, g.K);
   const int nparts = p.splits * p.tiles_n;

@@ -254,7 +254,7 @@ static hipError_t run_f32(const GemmDesc& g, const EpiArgs& ep, hipStream_t st) 
 // on widths that are multiples of 64.  The adaLN and FiLM products over a handful of samples stay with
 // the generic kernel.
 bool gemm_f32_takes(const GemmDesc& g, int epi) {
-  if (g.dtype != kF32 || g.N % 64 || g.a_type != kF32 || g.b_type != kF32) return false;
+  if (g.dtype != kF32 || g.N % 64) return false;
   switch (epi) {
     case EPI_BIAS_ACT: case EPI_RESID: case EPI_GELU: return g.a_kmajor && g.b_kmajor && g.K % 64 == 0;
     case EPI_DGELU: case EPI_ACT: case EPI_F32: case EPI_F32_ACC: return g.a_kmajor && !g.b_kmajor && g.K % 64 == 0;

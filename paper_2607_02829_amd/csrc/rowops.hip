@@ -264,39 +264,55 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const float* __restrict__ d
   }
 }
 
-// Per-sample column sums of X (or X * Y), in chunks of kColRows rows:
-// part[(b * nchunk + chunk) * N + c].  Optional per-sample column weights w[b*wstride + c].
+// The gate of a residual branch, backward, in one pass over X [B*S, N] (fp32, the gradient of the gated
+// branch): act = T(X * gate_b) for the branch's GEMMs, and the gate's gradient sum_s X * Y (Y the branch
+// output) as partial column sums of kColRows rows, part[(b * nchunk + chunk) * N + c].  Bound by reading
+// X and Y and writing act.  Lane l of a wave owns four columns, the four waves take the chunk's rows in
+// turn, eight rows' loads in flight each, and their sums are added in wave order.  Two kernels, one
+// thread per column down the rows and one elementwise, took 27.8 + 5.6 us at 2 x 2048 rows of 1024; this
+// one 9.1 (13.9 beside the second stream's weight gradients).
 constexpr int kColRows = 64;
-template <typename TX, typename TY>
-__global__ __launch_bounds__(256) void colsum_kernel(const TX* __restrict__ X, const TY* __restrict__ Y,
-                                                     const float* __restrict__ w, int wstride, int S, int N,
-                                                     float* __restrict__ part) {
-  const int c = blockIdx.x * 256 + threadIdx.x;
+template <typename T>
+__global__ __launch_bounds__(256) void gate_bwd_kernel(const float* __restrict__ X, const T* __restrict__ Y,
+                                                       const float* __restrict__ gate, int gstride, int S, int N,
+                                                       T* __restrict__ act, float* __restrict__ part) {
+  __shared__ f32x4 red[4][64];
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const int c = blockIdx.x * 256 + lane * 4;
   const int chunk = blockIdx.y, b = blockIdx.z, nchunk = gridDim.y;
-  if (c >= N) return;
   const int s0 = chunk * kColRows, s1 = min(S, s0 + kColRows);
-  float acc = 0.f;
-  // eight rows' loads in flight before their products are added, rows in ascending order
-  int s = s0;
-  for (; s + 8 <= s1; s += 8) {
-    float v[8];
+  float acc[4] = {0.f, 0.f, 0.f, 0.f};
+  if (c < N) {
+    float g[4];
+    ldv<4>(gate + (size_t)b * gstride + c, g);
+    for (int s = s0 + wid; s < s1; s += 32) {
+      float x[8][4], y[8][4];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const size_t o = ((size_t)b * S + s + i) * N + c;
-      v[i] = to_f32<TX>(X[o]);
-      if (Y) v[i] *= to_f32<TY>(Y[o]);
+      for (int i = 0; i < 8; ++i)
+        if (s + 4 * i < s1) {
+          const size_t o = ((size_t)b * S + s + 4 * i) * N + c;
+          ldv<4>(X + o, x[i]);
+          ldv<4>(Y + o, y[i]);
+        }
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (s + 4 * i < s1) {
+          const size_t o = ((size_t)b * S + s + 4 * i) * N + c;
+          float a[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            a[e] = x[i][e] * g[e];
+            acc[e] += x[i][e] * y[i][e];
+          }
+          stv<4>(act + o, a);
+        }
     }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) acc += v[i];
   }
-  for (; s < s1; ++s) {
-    const size_t o = ((size_t)b * S + s) * N + c;
-    float v = to_f32<TX>(X[o]);
-    if (Y) v *= to_f32<TY>(Y[o]);
-    acc += v;
-  }
-  if (w) acc *= w[(size_t)b * wstride + c];
-  part[((size_t)b * nchunk + chunk) * N + c] = acc;
+  red[wid][lane] = f32x4{acc[0], acc[1], acc[2], acc[3]};
+  __syncthreads();
+  if (wid == 0 && c < N)
+    *reinterpret_cast<f32x4*>(part + ((size_t)b * nchunk + chunk) * N + c) =
+        red[0][lane] + red[1][lane] + red[2][lane] + red[3][lane];
 }
 
 // y = T(x) elementwise (storage -> fp32, fp32 -> storage, fp32 -> activation), with an
@@ -523,18 +539,15 @@ hipError_t launch_ln_bwd(int dtype, const float* du, const float* x, const float
 
 int colsum_chunks(int S) { return (S + kColRows - 1) / kColRows; }
 
-// X type: 0 = fp32, 1 = bf16; Y likewise (Y may be null).
-hipError_t launch_colsum(int xt, const void* X, int yt, const void* Y, const float* w, int wstride, int B, int S,
-                         int N, float* part, hipStream_t st) {
+hipError_t launch_gate_bwd(int dtype, const float* X, const void* Y, const float* gate, int gstride, int B, int S,
+                           int N, void* act, float* part, hipStream_t st) {
+  if (N % 4 != 0) return hipErrorInvalidValue;
   dim3 g((N + 255) / 256, colsum_chunks(S), B);
-#define SR_COLSUM(TX, TY) \
-  SR_LAUNCH((colsum_kernel<TX, TY>), g, dim3(256), 0, st, (const TX*)X, (const TY*)Y, w, wstride, S, N, part)
-  if (xt == kBF16) {
-    if (yt == kBF16) SR_COLSUM(bf16_t, bf16_t); else SR_COLSUM(bf16_t, float);
-  } else {
-    if (yt == kBF16) SR_COLSUM(float, bf16_t); else SR_COLSUM(float, float);
-  }
-#undef SR_COLSUM
+  if (dtype == kBF16)
+    SR_LAUNCH(gate_bwd_kernel<bf16_t>, g, dim3(256), 0, st, X, (const bf16_t*)Y, gate, gstride, S, N, (bf16_t*)act,
+              part);
+  else
+    SR_LAUNCH(gate_bwd_kernel<float>, g, dim3(256), 0, st, X, (const float*)Y, gate, gstride, S, N, (float*)act, part);
   return hipGetLastError();
 }
 

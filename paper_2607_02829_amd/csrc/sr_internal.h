@@ -18,7 +18,6 @@ enum {
   EPI_ACT = 4,
   EPI_F32 = 5,
   EPI_F32_ACC = 6,
-  EPI_BIAS_F32 = 7,
   EPI_DW = 8,
   EPI_DO = 9,   // dO store plus the attention row statistic delta (head dim 64)
 };
@@ -65,8 +64,7 @@ struct GemmDesc {
   size_t a_bytes = 0, b_bytes = 0;  // exact sizes of the operands (bounds of the buffer loads)
   bool a_kmajor = true, b_kmajor = true;
   bool use_mfma = false;
-  int dtype = kBF16;          // storage type (bias / residual output)
-  int a_type = kBF16, b_type = kBF16;
+  int dtype = kBF16;          // type of the operands, bias and storage output
 };
 
 hipError_t launch_select_random(int rows, int L, int K, uint64_t seed, uint64_t step, int32_t* idx, hipStream_t st);
@@ -125,8 +123,9 @@ hipError_t launch_ln_bwd(int dtype, const float* du, const float* x, const float
                          const void* gamma, const float* mod, int mod_off, const float* dres, int B, int S, int D,
                          float* dx, void* dx_act, float* part, hipStream_t st);
 int colsum_chunks(int S);
-hipError_t launch_colsum(int xt, const void* X, int yt, const void* Y, const float* w, int wstride, int B, int S,
-                         int N, float* part, hipStream_t st);
+// act = T(X * gate_b) and the partial column sums of X * Y (rows of part: colsum_chunks(S) per sample)
+hipError_t launch_gate_bwd(int dtype, const float* X, const void* Y, const float* gate, int gstride, int B, int S,
+                           int N, void* act, float* part, hipStream_t st);
 hipError_t launch_convert(int ti, const void* x, int to, void* y, size_t n, const float* w, int wstride, int S, int D,
                           float* y32, hipStream_t st);
 hipError_t launch_reduce_cols(const float* part, int R, int G, int sum_groups, int width, int half, float* out_lo,
@@ -138,6 +137,9 @@ hipError_t launch_reduce_cols(const float* part, int R, int G, int sum_groups, i
 hipError_t launch_gemv_rows(int dtype, const void* x, int ldx, const void* W, const void* bias, int B, int J, int Dd,
                             float* y, int ldy, hipStream_t st);
 size_t gemv_cols_scratch(int B, int J, int N);
+// out[j][n] = sum_b x[b * ldx + j] c[b][n] (fp32; c of the storage type), j < J, n < N
+hipError_t launch_outer(int dtype, const float* x, int ldx, const void* c, int B, int J, int N, float* out,
+                        hipStream_t st);
 hipError_t launch_gemv_cols(int dtype, const float* x, int ldx, const void* W, int B, int J, int N, float* y,
                             int accumulate, float* part, hipStream_t st);
 hipError_t launch_fill_f32(float* p, size_t n, float v, hipStream_t st);

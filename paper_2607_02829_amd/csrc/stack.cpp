@@ -64,7 +64,6 @@ GemmDesc desc(const Dims& d, const void* A, bool ak, long long lda, size_t abyte
   g.a_kmajor = ak; g.b_kmajor = bk;
   g.use_mfma = d.dtype == kBF16;
   g.dtype = d.dtype;
-  g.a_type = d.dtype; g.b_type = d.dtype;
   return g;
 }
 
@@ -266,11 +265,11 @@ hipError_t weight_grad(const char* name, const Dims& d, const void* dY, int N, c
   return launch_weight_grad(g, dw, db, sc.wpart[kind], sc.dbpart[kind], st, job);
 }
 
-// dmod[b, off + c] = sum_s X[b,s,c] * Y[b,s,c]  (adaLN gate gradients)
-hipError_t gate_grad(const Dims& d, const float* X, const void* Y, float* dmod, int off, const Scratch& sc,
-                     hipStream_t st) {
-  ProfScope ps("colsum", 0, (double)d.M * d.D * (4 + d.elt), st);
-  SR_TRY(launch_colsum(kF32, X, d.dtype, Y, nullptr, 0, d.B, d.S, d.D, sc.part, st));
+// act = X * gate_b (storage copy) and dmod[b, off + c] = sum_s X[b,s,c] * Y[b,s,c]  (adaLN gates)
+hipError_t gate_bwd(const Dims& d, const float* X, const void* Y, const float* gate, void* act, float* dmod, int off,
+                    const Scratch& sc, hipStream_t st) {
+  ProfScope ps("colsum", 0, (double)d.M * d.D * (4 + 2 * d.elt), st);
+  SR_TRY(launch_gate_bwd(d.dtype, X, Y, gate, 6 * d.D, d.B, d.S, d.D, act, sc.part, st));
   return launch_reduce_cols(sc.part, colsum_chunks(d.S), d.B, 0, d.D, d.D, dmod + off, nullptr, 6 * d.D, st);
 }
 
@@ -443,9 +442,7 @@ hipError_t stack_bwd(const Dims& d, const sr_block_params* p, const void* cond, 
       if (ada) {
         // MLP-branch gradient dm = dh' * gate2 (activation copy) and dgate2 = sum_s dh' * m_out
         SR_TRY(join(kFc2));   // g0 may still be read by the previous block's dW_fc2
-        ProfScope ps("convert", 0, (double)M * D * (e + 4), st);
-        SR_TRY(launch_convert(kF32, sc.g_res, d.dtype, g0, (size_t)M * D, s.mod + 5 * D, 6 * D, S, D, nullptr, st));
-        SR_TRY(gate_grad(d, sc.g_res, s.m_out, sc.dmod, 5 * D, sc, st));
+        SR_TRY(gate_bwd(d, sc.g_res, s.m_out, s.mod + 5 * D, g0, sc.dmod, 5 * D, sc, st));
       }
       // FC2: dW2, db2; dz = (dm W2) * GELU'(z)
       SR_TRY(on_side(kFc2, [&](hipStream_t ss) -> hipError_t {
@@ -493,10 +490,8 @@ hipError_t stack_bwd(const Dims& d, const sr_block_params* p, const void* cond, 
       }
       if (ada) {
         // attention-branch gradient da = dh1 * gate1 and dgate1 = sum_s dh1 * a_out
-        SR_TRY(gate_grad(d, sc.g_res2, s.a_out, sc.dmod, 2 * D, sc, st));
         SR_TRY(join(kO));   // g1 may still be read by the previous block's dW_o
-        ProfScope ps("convert", 0, (double)M * D * (e + 4), st);
-        SR_TRY(launch_convert(kF32, sc.g_res2, d.dtype, g1, (size_t)M * D, s.mod + 2 * D, 6 * D, S, D, nullptr, st));
+        SR_TRY(gate_bwd(d, sc.g_res2, s.a_out, s.mod + 2 * D, g1, sc.dmod, 2 * D, sc, st));
       }
       // output projection: dWo, dbo; dO = da Wo (with the attention row statistic
       // delta = rowsum(dO * O) per head in the same epilogue when the head dim is 64)
@@ -564,11 +559,7 @@ hipError_t stack_bwd(const Dims& d, const sr_block_params* p, const void* cond, 
         // dW_ada = dmod^T c ; db_ada = sum_b dmod ; dcond (+)= dmod W_ada
         ProfScope ps("mod", 0, 0, st);
         if (g.w_ada) {
-          GemmDesc gd = desc(d, sc.dmod, false, 6 * D, (size_t)d.B * 6 * D * 4, cond, false, D, (size_t)d.B * D * e,
-                             6 * D, D, d.B);
-          gd.use_mfma = false; gd.a_type = kF32;
-          EpiArgs ep; ep.out_f32 = g.w_ada; ep.ldo = D;
-          SR_TRY(launch_gemm(gd, EPI_F32, ep, st));
+          SR_TRY(launch_outer(d.dtype, sc.dmod, 6 * D, cond, d.B, 6 * D, D, g.w_ada, st));
         }
         if (g.b_ada) SR_TRY(launch_reduce_cols(sc.dmod, d.B, 1, 1, 6 * D, 6 * D, g.b_ada, nullptr, 0, st));
         if (dcond)   // dcond (+)= dmod W_ada, summed over the blocks in backward order
