@@ -740,8 +740,16 @@ struct DwPlan {
 };
 static DwPlan dw_plan(int M, int N, int K) {
   DwPlan p;
+  // Measured on MI355X (us, reduction included): up to some 8000 tokens 64 x 128 tiles while they fit one
+  // round (1024 x 1024 over 4050 tokens 23.2, 128 x 128 in four runs 28.7; 2048 x 1024 over 1024 13.8, 17.6),
+  // then 128 x 128.  Over more tokens the larger tile's fewer operand bytes outweigh its partial planes:
+  // over 16384, 2048 x 1024 121 -> 94 in two runs of 128 x 128, 1024 x 1024 66 -> 55 in four; from 192 tiles
+  // two workgroups per CU in two runs, 4096 x 1024 166 -> 155, 3072 x 1024 152 -> 136 (over 4050 tokens one
+  // run at one per CU stays ahead, 46.6 against 52.8).
   const long t = tile_count(T128x128, M, N);
-  p.shape = t >= 384 ? T128x128x2 : t >= 192 ? T128x128 : T64x128;
+  if (K >= 8192 && t >= 32) p.shape = t >= 192 ? T128x128x2 : T128x128;
+  else if (t >= 192) p.shape = t >= 384 ? T128x128x2 : T128x128;
+  else p.shape = tile_count(T64x128, M, N) <= 256 ? T64x128 : T128x128;
 #ifdef SR_GEMM_FORCE_SHAPE
   if (g_force_shape >= 0) p.shape = g_force_shape;
 #endif
