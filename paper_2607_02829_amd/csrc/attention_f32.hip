@@ -2,9 +2,9 @@
 // dQ at head dims 32, 64 and 128, on separate query and key/value buffers (self-attention passes the
 // one token-major qkv buffer twice).  Formulas and layouts as in attention.hip.
 //
-// A workgroup of four waves owns 32 rows of the resident dimension; its waves take the 32-row units of
-// the streamed one in turn (unit u belongs to wave u mod 4) and their results are merged through LDS in
-// wave order at the end, so a few hundred tokens already give every SIMD a wave, and results do not
+// A workgroup of kW waves, four or eight, owns 32 rows of the resident dimension; its waves take the
+// 32-row units of the streamed one in turn (unit u belongs to wave u mod kW) and their results are merged
+// through LDS in wave order at the end, so a few hundred tokens already give every SIMD a wave, and results do not
 // depend on scheduling.  A unit has HD MFMAs of 64 cycles per product pair (forward: 4096 cycles at
 // head dim 64) for HD / 8 16-byte row loads and HD / 2 4-byte column loads per lane, so the operands
 // come straight from global memory (each element once per workgroup, from L2) without LDS.
@@ -20,7 +20,8 @@ namespace sr {
 
 namespace {
 
-constexpr int kW = 4;   // waves sharing a workgroup's rows
+// workgroups per CU: two waves per SIMD, one at head dim 128 (its registers)
+constexpr int f32_occ(int hd, int kw) { return kw == 8 || hd == 128 ? 1 : 2; }
 
 SR_DEV f32x16 mfma32(float a, float b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
 SR_DEV int srow(int r, int h) { return 8 * (r >> 2) + 4 * h + (r & 3); }
@@ -91,7 +92,7 @@ SR_DEV void to_plane(float* pl, const f32x16 (&acc)[HD / 32], int l32, int h) {
     }
 }
 // The waves' planes added in wave order, scaled, to rows r0 .. of dst.
-template <int HD>
+template <int HD, int kW>
 SR_DEV void merge(const float* planes, float* dst, size_t ld, int r0, int n, float scale) {
   for (int c = threadIdx.x; c < 32 * HD / 4; c += 64 * kW) {
     const int row = c / (HD / 4), col = c % (HD / 4) * 4;
@@ -107,8 +108,8 @@ SR_DEV void merge(const float* planes, float* dst, size_t ld, int r0, int n, flo
 
 // q: Sq rows (stride ldq), kv: Skv rows (stride ldkv, values D columns on), *_elems: elements
 // addressable from each pointer.
-template <int HD>
-__global__ __launch_bounds__(64 * kW, HD == 128 ? 1 : 2) void attn_fwd_f32(const float* __restrict__ q, int ldq, uint32_t q_elems,
+template <int HD, int kW>
+__global__ __launch_bounds__(64 * kW, f32_occ(HD, kW)) void attn_fwd_f32(const float* __restrict__ q, int ldq, uint32_t q_elems,
                                                        const float* __restrict__ kv, int ldkv, uint32_t kv_elems,
                                                        float* __restrict__ O, float* __restrict__ lse, int Sq, int Skv,
                                                        int H, int D, float sl2) {
@@ -170,12 +171,12 @@ __global__ __launch_bounds__(64 * kW, HD == 128 ? 1 : 2) void attn_fwd_f32(const
   to_plane<HD>(planes + wid * 32 * plane_ld<HD>(), o, l32, h);
   if (wid == 0 && h == 0 && q0 + l32 < Sq) lse[((size_t)b * H + hh) * Sq + q0 + l32] = mx + log2f(tot);
   __syncthreads();
-  merge<HD>(planes, O + (size_t)b * Sq * D + hh * HD, D, q0, Sq, 1.0f);
+  merge<HD, kW>(planes, O + (size_t)b * Sq * D + hh * HD, D, q0, Sq, 1.0f);
 }
 
 // dK to dk_out (row stride ldo), dV D columns after it.
-template <int HD>
-__global__ __launch_bounds__(64 * kW, HD == 128 ? 1 : 2) void attn_dkv_f32(const float* __restrict__ q, int ldq, uint32_t q_elems,
+template <int HD, int kW>
+__global__ __launch_bounds__(64 * kW, f32_occ(HD, kW)) void attn_dkv_f32(const float* __restrict__ q, int ldq, uint32_t q_elems,
                                                        const float* __restrict__ kv, int ldkv, uint32_t kv_elems,
                                                        const float* __restrict__ dO, const float* __restrict__ lse,
                                                        const float* __restrict__ delta, float* __restrict__ dk_out,
@@ -224,15 +225,15 @@ __global__ __launch_bounds__(64 * kW, HD == 128 ? 1 : 2) void attn_dkv_f32(const
   float* out = dk_out + (size_t)b * Skv * ldo + hh * HD;
   to_plane<HD>(planes + wid * 32 * plane_ld<HD>(), dk, l32, h);
   __syncthreads();
-  merge<HD>(planes, out, ldo, k0, Skv, scale);
+  merge<HD, kW>(planes, out, ldo, k0, Skv, scale);
   __syncthreads();
   to_plane<HD>(planes + wid * 32 * plane_ld<HD>(), dv, l32, h);
   __syncthreads();
-  merge<HD>(planes, out + D, ldo, k0, Skv, 1.0f);
+  merge<HD, kW>(planes, out + D, ldo, k0, Skv, 1.0f);
 }
 
-template <int HD>
-__global__ __launch_bounds__(64 * kW, HD == 128 ? 1 : 2) void attn_dq_f32(const float* __restrict__ q, int ldq, uint32_t q_elems,
+template <int HD, int kW>
+__global__ __launch_bounds__(64 * kW, f32_occ(HD, kW)) void attn_dq_f32(const float* __restrict__ q, int ldq, uint32_t q_elems,
                                                       const float* __restrict__ kv, int ldkv, uint32_t kv_elems,
                                                       const float* __restrict__ dO, const float* __restrict__ lse,
                                                       const float* __restrict__ delta, float* __restrict__ dq_out,
@@ -275,17 +276,28 @@ __global__ __launch_bounds__(64 * kW, HD == 128 ? 1 : 2) void attn_dq_f32(const 
   }
   to_plane<HD>(planes + wid * 32 * plane_ld<HD>(), dq, l32, h);
   __syncthreads();
-  merge<HD>(planes, dq_out + (size_t)b * Sq * ldo + hh * HD, ldo, q0, Sq, scale);
+  merge<HD, kW>(planes, dq_out + (size_t)b * Sq * ldo + hh * HD, ldo, q0, Sq, scale);
 }
 
 // ------------------------------------------------------------------------------ launchers
 
-#define SR_F32_HD(KERNEL, GRID, ...)                                                                        \
+// Eight waves where four would leave the SIMDs one wave each (a round of workgroups at most, which then
+// have no second one beside them) and every wave still has a unit: one wave's operand loads fly under the
+// other's MFMAs.  2 x 1013 tokens, four heads of 64, 256 workgroups: forward 33.5 -> 29.5, dK/dV 64 ->
+// 58, dQ 44 -> 39 us.
+static bool eight_waves(int rows, int streamed, int H, int B) {
+  return (long)((rows + 31) / 32) * H * B <= 256 && streamed > 32 * 7;
+}
+
+#define SR_F32_HD(KERNEL, ROWS, STREAMED, ...)                                                              \
   do {                                                                                                      \
-    const dim3 g_ = (GRID);                                                                                 \
-    if (hd == 32) SR_LAUNCH((KERNEL<32>), g_, dim3(64 * kW), 0, st, __VA_ARGS__);                           \
-    else if (hd == 64) SR_LAUNCH((KERNEL<64>), g_, dim3(64 * kW), 0, st, __VA_ARGS__);                      \
-    else SR_LAUNCH((KERNEL<128>), g_, dim3(64 * kW), 0, st, __VA_ARGS__);                                   \
+    const dim3 g_((unsigned)(((ROWS) + 31) / 32), H, B);                                                    \
+    const bool w8_ = eight_waves(ROWS, STREAMED, H, B);                                                     \
+    if (hd == 32 && w8_) SR_LAUNCH((KERNEL<32, 8>), g_, dim3(512), 0, st, __VA_ARGS__);                     \
+    else if (hd == 32) SR_LAUNCH((KERNEL<32, 4>), g_, dim3(256), 0, st, __VA_ARGS__);                       \
+    else if (hd == 64 && w8_) SR_LAUNCH((KERNEL<64, 8>), g_, dim3(512), 0, st, __VA_ARGS__);                \
+    else if (hd == 64) SR_LAUNCH((KERNEL<64, 4>), g_, dim3(256), 0, st, __VA_ARGS__);                       \
+    else SR_LAUNCH((KERNEL<128, 4>), g_, dim3(256), 0, st, __VA_ARGS__);                                    \
     const hipError_t e_ = hipGetLastError();                                                                \
     if (e_ != hipSuccess) return e_;                                                                        \
   } while (0)
@@ -293,7 +305,7 @@ __global__ __launch_bounds__(64 * kW, HD == 128 ? 1 : 2) void attn_dq_f32(const 
 hipError_t launch_attn_fwd_f32(const float* q, int ldq, uint32_t q_elems, const float* kv, int ldkv, uint32_t kv_elems,
                                float* O, float* lse, int B, int Sq, int Skv, int H, int D, hipStream_t st) {
   const int hd = D / H;
-  SR_F32_HD(attn_fwd_f32, dim3((Sq + 31) / 32, H, B), q, ldq, q_elems, kv, ldkv, kv_elems, O, lse, Sq, Skv, H, D,
+  SR_F32_HD(attn_fwd_f32, Sq, Skv, q, ldq, q_elems, kv, ldkv, kv_elems, O, lse, Sq, Skv, H, D,
             1.4426950408889634f / sqrtf((float)hd));
   return hipSuccess;
 }
@@ -303,9 +315,9 @@ hipError_t launch_attn_bwd_f32(const float* q, int ldq, uint32_t q_elems, const 
                                int ld_dk, int B, int Sq, int Skv, int H, int D, hipStream_t st) {
   const int hd = D / H;
   const float scale = 1.0f / sqrtf((float)hd), sl2 = 1.4426950408889634f * scale;
-  SR_F32_HD(attn_dkv_f32, dim3((Skv + 31) / 32, H, B), q, ldq, q_elems, kv, ldkv, kv_elems, dO, lse, delta, dk, ld_dk,
+  SR_F32_HD(attn_dkv_f32, Skv, Sq, q, ldq, q_elems, kv, ldkv, kv_elems, dO, lse, delta, dk, ld_dk,
             Sq, Skv, H, D, sl2, scale);
-  SR_F32_HD(attn_dq_f32, dim3((Sq + 31) / 32, H, B), q, ldq, q_elems, kv, ldkv, kv_elems, dO, lse, delta, dq, ld_dq,
+  SR_F32_HD(attn_dq_f32, Sq, Skv, q, ldq, q_elems, kv, ldkv, kv_elems, dO, lse, delta, dq, ld_dq,
             Sq, Skv, H, D, sl2, scale);
   return hipSuccess;
 }
