@@ -7,9 +7,9 @@
 // dW = dY^T X is m-major x n-major (the reduction runs over tokens).
 //
 // gemm_mfma: bf16 operands, fp32 accumulation on gfx950 matrix cores
-// (v_mfma_f32_32x32x16_bf16).  Workgroup tiles of 128 x 128 down to 32 x 32 by 64 k,
-// four waves in a 2 x 2 arrangement on the larger ones; on the smaller ones two to eight
-// groups of waves share the k range (pick_shape).  Operand tiles go global -> LDS directly,
+// (v_mfma_f32_32x32x16_bf16).  Workgroup tiles of 128 x 128 down to 32 x 32 by 64 k, eight
+// waves: in a 2 x 4 arrangement on the larger ones, on the smaller ones in two to eight groups
+// that share the k range (pick_shape).  Operand tiles go global -> LDS directly,
 // their 16-byte chunks at XOR-swizzled positions; m- and n-major ones are transposed by the
 // LDS read.  Two to four k-tiles are in flight while the current one is consumed.
 // Global loads go through buffer resources, so rows past the end of an operand
@@ -373,7 +373,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, OCC) void gemm_mfma_kernel(const
   // EPI_DW bias gradient: row sums of A (r-major there: k-rows of BM values).  The tile row's
   // tiles_n workgroups share the work: workgroup tn sums the k-tiles t with t % tiles_n == tn.
   // Thread: chunk position cp of k-rows kg, kg + DBG, ...; eight running sums.
-  constexpr int CPR = BM / 8, DBG = 256 / CPR;
+  constexpr int CPR = BM / 8, DBG = EPI == EPI_DW ? NT / CPR : 64;
   const bool want_db = EPI == EPI_DW && ep.db_out != nullptr;
   float dbv[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   const uint32_t db_addr = sbase + (uint32_t)(((threadIdx.x / CPR) * BM + (threadIdx.x % CPR) * 8) * 2);
@@ -642,15 +642,27 @@ static hipError_t launch_reduce(const float* part, int splits, size_t n, float* 
 
 // ============================================================================ dispatch
 
-// Tile shapes of the MFMA kernel: rows x columns, k groups, stages and workgroups per CU.
-enum TileShape { T128x128x2, T128x128, T64x128, T64x64g2, T32x64g4, T32x32g8 };
+// Tile shapes of the MFMA kernel: rows x columns, k groups, workgroups per CU.  Eight waves each, so
+// that a SIMD has two even at one workgroup per CU: one's LDS reads and epilogue run under the other's
+// MFMAs.  Against four waves of twice the tile (us; M x N x K): one workgroup per CU 1024 x 3072 x 1024
+// 14.0 -> 12.1, 4050 x 1024 x 1024 18.8 -> 15.3 (dO), 4050 x 1024 x 4096 48.0 -> 45.3; two per CU 2048 x
+// 3072 x 1024 21.7 -> 18.8, 4050 x 4096 x 1024 60.8 -> 58.0 (GELU); 64 x 128 2048 x 1024 x 4096 26.6 ->
+// 24.8; weight gradients 3072 x 1024 over 1024 tokens 19.5 -> 17.4, over 4050 43.1 -> 39.8.  Sixteen
+// waves, and tiles of 256 x 128 and 128 x 256, lie within 3 % of these or behind but for the 1024-column
+// products of 16200 tokens (153 against 164).
+// Two shapes stay at four waves (w4) where kernels of the two streams share the CUs and the second wave
+// per SIMD delays the other stream's more than it gains: weight gradients on 128 x 128 tiles over more
+// than 2048 tokens (adaLN step at 4096 tokens 804 -> 782 us, 12-block step at 4050 9350 -> 9330; at 1024
+// tokens eight are ahead, 1875 against 1895), and two workgroups per CU past two rounds of them (dense
+// block of 16200 tokens 6300 -> 6262; at 4050 tokens eight are ahead, 9350 against 9415).
+enum TileShape { T128x128x2, T128x128x2w4, T128x128, T128x128w4, T64x128, T64x64g2, T32x64g4, T32x32g8 };
 struct ShapeInfo {
   int bm, bn, occ;
 };
 static ShapeInfo shape_info(int s) {
   switch (s) {
-    case T128x128x2: return {128, 128, 2};
-    case T128x128: return {128, 128, 1};
+    case T128x128x2: case T128x128x2w4: return {128, 128, 2};
+    case T128x128: case T128x128w4: return {128, 128, 1};
     case T64x128: return {64, 128, 1};
     case T32x64g4: return {32, 64, 1};
     case T32x32g8: return {32, 32, 1};
@@ -680,11 +692,14 @@ static hipError_t run_mfma_tile(const GemmDesc& g, const EpiArgs& ep, int splits
 template <int EPI, typename T, typename Ta>
 static hipError_t run_shape(int shape, const GemmDesc& g, const EpiArgs& ep, int splits, int kps, hipStream_t st) {
   switch (shape) {
-    case T128x128: return run_mfma_tile<128, 128, 2, 2, 1, 4, 1, EPI, T, Ta>(g, ep, splits, kps, st);
-    case T128x128x2: return run_mfma_tile<128, 128, 2, 2, 1, 2, 2, EPI, T, Ta>(g, ep, splits, kps, st);
-    case T64x128: return run_mfma_tile<64, 128, 2, 2, 1, 4, 1, EPI, T, Ta>(g, ep, splits, kps, st);
+    case T128x128: return run_mfma_tile<128, 128, 2, 4, 1, 4, 1, EPI, T, Ta>(g, ep, splits, kps, st);
+    case T128x128x2: return run_mfma_tile<128, 128, 2, 4, 1, 2, 2, EPI, T, Ta>(g, ep, splits, kps, st);
+    case T128x128x2w4: return run_mfma_tile<128, 128, 2, 2, 1, 2, 2, EPI, T, Ta>(g, ep, splits, kps, st);
+    case T64x128: return run_mfma_tile<64, 128, 2, 4, 1, 4, 1, EPI, T, Ta>(g, ep, splits, kps, st);
     default: break;
   }
+  if constexpr (EPI == EPI_DW)
+    if (shape == T128x128w4) return run_mfma_tile<128, 128, 2, 2, 1, 4, 1, EPI, T, Ta>(g, ep, splits, kps, st);
   if constexpr (EPI != EPI_DW) {
     switch (shape) {
       case T64x64g2: return run_mfma_tile<64, 64, 2, 2, 2, 4, 1, EPI, T, Ta>(g, ep, splits, kps, st);
@@ -706,17 +721,17 @@ static long tile_count(int s, int M, int N) {
 // the 256 CUs.  With fewer tiles than CUs a launch lasts as long as one workgroup, so a smaller
 // tile with its k range shared by more waves is faster; past one round the larger tile is, as it
 // fetches fewer operand bytes per output.  Measured on MI355X (us; M x N x K):
-//   128 x 1024 x 4096: 64 x 128 20.0, 64 x 64 with two groups 13.4, 32 x 64 with four 11.2,
+//   128 x 1024 x 4096: 64 x 128 19.0, 64 x 64 with two groups 13.4, 32 x 64 with four 11.2,
 //   32 x 32 with eight (128 tiles) 10.2;  128 x 3072 x 1024: 8.0, 6.4, 6.0 (192 tiles), 8.5 (384)
-//   512 x 1024 x 4096: 20.5, 14.4, 12.1 (256), 19.0 (512);  1024 x 1024 x 4096: 21.2, 15.7 (256),
-//   22.1 (512);  2048 x 1024 x 4096: 24.8 (256), 29.9 (512), 128 x 128 34.6 (128)
-//   1024 x 3072 x 1024: 64 x 128 14.8 (384), 128 x 128 13.0 (192)
+//   512 x 1024 x 4096: 19.6, 14.4, 12.1 (256), 19.0 (512);  1024 x 1024 x 4096: 19.6, 15.7 (256),
+//   22.1 (512);  2048 x 1024 x 4096: 24.8 (256), 29.9 (512), 128 x 128 29.8 (128)
+//   1024 x 3072 x 1024: 64 x 128 14.4 (384), 128 x 128 12.1 (192)
 // Past one round of 128 x 128 tiles, two workgroups per CU: one's epilogue overlaps the other's
-// MFMAs (2048 x 3072 x 1024: 24.8 -> 21.5; 4050 x 4096 x 1024 with GELU: 72 -> 57).
+// MFMAs (2048 x 3072 x 1024: 20.6 -> 18.8; 4050 x 4096 x 1024 with GELU: 69.6 -> 58.0).
 static int pick_shape(int M, int N, bool whole_heads) {
   for (int s : {T32x32g8, T32x64g4, T64x64g2, T64x128, T128x128})
     if (!(s == T32x32g8 && whole_heads) && tile_count(s, M, N) <= 256) return s;
-  return T128x128x2;
+  return tile_count(T128x128, M, N) <= 1024 ? T128x128x2 : T128x128x2w4;
 }
 
 #ifdef SR_GEMM_FORCE_SHAPE
@@ -747,9 +762,10 @@ static DwPlan dw_plan(int M, int N, int K) {
   // two workgroups per CU in two runs, 4096 x 1024 166 -> 155, 3072 x 1024 152 -> 136 (over 4050 tokens one
   // run at one per CU stays ahead, 46.6 against 52.8).
   const long t = tile_count(T128x128, M, N);
-  if (K >= 8192 && t >= 32) p.shape = t >= 192 ? T128x128x2 : T128x128;
-  else if (t >= 192) p.shape = t >= 384 ? T128x128x2 : T128x128;
-  else p.shape = tile_count(T64x128, M, N) <= 256 ? T64x128 : T128x128;
+  const int one = K > 2048 ? T128x128w4 : T128x128;
+  if (K >= 8192 && t >= 32) p.shape = t >= 192 ? T128x128x2w4 : one;
+  else if (t >= 192) p.shape = t >= 384 ? (K > 2048 ? T128x128x2w4 : T128x128x2) : one;
+  else p.shape = tile_count(T64x128, M, N) <= 256 ? T64x128 : one;
 #ifdef SR_GEMM_FORCE_SHAPE
   if (g_force_shape >= 0) p.shape = g_force_shape;
 #endif
