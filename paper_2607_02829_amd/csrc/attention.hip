@@ -272,11 +272,14 @@ SR_DEV void unstage(const bf16_t* stage, bf16_t* dst, size_t ld, int r0, int S) 
 struct TileId {
   int blk, h, b;
 };
-SR_DEV TileId xcd_tile_id() {
-  const int nb = gridDim.x, nh = gridDim.y, n = nb * nh * gridDim.z;
-  int l = blockIdx.x + nb * (blockIdx.y + nh * blockIdx.z);
+SR_DEV TileId xcd_tile_id(int l, int nb, int nh, int nz) {   // l: linear index of the nb x nh x nz tiles
+  const int n = nb * nh * nz;
   if ((n & 7) == 0) l = (l & 7) * (n >> 3) + (l >> 3);
   return {l % nb, (l / nb) % nh, l / (nb * nh)};
+}
+
+SR_DEV TileId xcd_tile_id() {
+  return xcd_tile_id(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), gridDim.x, gridDim.y, gridDim.z);
 }
 
 // Split calls: the streamed dimension is cut into nsplit runs of whole tiles, one workgroup each (run
@@ -502,13 +505,19 @@ __global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_fwd_mfma(const
   unstage<HD, NW>(smem, O + (size_t)b * Sq * D + hh * HD, D, run.blk * (32 * NW), Sq);
 }
 
+// LDS of the backward kernels: NSTG stages of two tiles, and (dK/dV) of their rows' lse and delta.
+template <int HD>
+constexpr int kBwdStage = NSTG * 2 * Geo<HD>::TE;
+constexpr int kBwdRows = NSTG * 2 * KT;
+
 // ------------------------------------------------------------------------------ backward dK, dV
 
 // NW waves (32 keys each) per workgroup share the Q / dO tiles.
-template <int HD, int NW, bool SPLIT>
 // Keys: Skv rows of kv (stride ldkv, values D columns on); queries: Sq rows of q (stride ldq,
 // q_elems addressable elements); dK to dk_out (stride ldo), dV D columns after it.
-__global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_bwd_dkv_mfma(const bf16_t* __restrict__ q, int ldq,
+// id: the workgroup's row block, head and sample of nB; smem, fsm: kBwdStage and kBwdRows elements of LDS.
+template <int HD, int NW, bool SPLIT>
+SR_DEV void attn_bwd_dkv(const TileId id, int nB, bf16_t* smem, float* fsm, const bf16_t* __restrict__ q, int ldq,
                                                          uint32_t q_elems, const bf16_t* __restrict__ kv, int ldkv,
                                                          const bf16_t* __restrict__ dO,
                                                          const float* __restrict__ lse, const float* __restrict__ delta,
@@ -516,10 +525,7 @@ __global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_bwd_dkv_mfma(c
                                                          int D, float sl2, float scale, int nsplit, AttnPart part) {
   using G = Geo<HD>;
   constexpr int TE = G::TE, KS = G::KS, DB = G::DB;
-  __shared__ __attribute__((aligned(16))) bf16_t smem[NSTG * 2 * TE];   // stage: Q tile, dO tile
-  __shared__ __attribute__((aligned(16))) float fsm[NSTG * 2 * KT];     // stage: lse, delta of the tile's rows
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, l32 = lane & 31, h32 = lane >> 5;
-  const TileId id = xcd_tile_id();
   const int b = id.b, hh = id.h;
   const bf16_t* kp = kv + (size_t)b * Skv * ldkv + hh * HD;
   const bf16_t* vp = kp + D;
@@ -541,9 +547,9 @@ __global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_bwd_dkv_mfma(c
   for (int db = 0; db < DB; ++db) { zero16(dv[db]); zero16(dk[db]); }
 
   const __amdgpu_buffer_rsrc_t rq = make_rsrc(q, q_elems * 2u);
-  const __amdgpu_buffer_rsrc_t rd = make_rsrc(dO, (uint32_t)((size_t)gridDim.z * Sq * D * 2));
-  const __amdgpu_buffer_rsrc_t rl = make_rsrc(lse, (uint32_t)((size_t)gridDim.z * H * Sq * 4));
-  const __amdgpu_buffer_rsrc_t rdl = make_rsrc(delta, (uint32_t)((size_t)gridDim.z * H * Sq * 4));
+  const __amdgpu_buffer_rsrc_t rd = make_rsrc(dO, (uint32_t)((size_t)nB * Sq * D * 2));
+  const __amdgpu_buffer_rsrc_t rl = make_rsrc(lse, (uint32_t)((size_t)nB * H * Sq * 4));
+  const __amdgpu_buffer_rsrc_t rdl = make_rsrc(delta, (uint32_t)((size_t)nB * H * Sq * 4));
   const uint32_t qbase = (uint32_t)(((size_t)b * Sq * ldq + hh * HD) * 2);
   const uint32_t dbase = (uint32_t)(((size_t)b * Sq * D + hh * HD) * 2);
   const uint32_t lbase = (uint32_t)(((size_t)b * H + hh) * Sq * 4);
@@ -670,6 +676,19 @@ __global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_bwd_dkv_mfma(c
   stage_t<HD>(smem, dv, 1.0f, wid, lane);
   __syncthreads();
   unstage<HD, NW>(smem, out + D + hh * HD, ldo, run.blk * (32 * NW), Skv);
+}
+
+template <int HD, int NW, bool SPLIT>
+__global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_bwd_dkv_mfma(const bf16_t* __restrict__ q, int ldq,
+                                                         uint32_t q_elems, const bf16_t* __restrict__ kv, int ldkv,
+                                                         const bf16_t* __restrict__ dO,
+                                                         const float* __restrict__ lse, const float* __restrict__ delta,
+                                                         bf16_t* __restrict__ dk_out, int ldo, int Sq, int Skv, int H,
+                                                         int D, float sl2, float scale, int nsplit, AttnPart part) {
+  __shared__ __attribute__((aligned(16))) bf16_t smem[kBwdStage<HD>];
+  __shared__ __attribute__((aligned(16))) float fsm[kBwdRows];
+  attn_bwd_dkv<HD, NW, SPLIT>(xcd_tile_id(), gridDim.z, smem, fsm, q, ldq, q_elems, kv, ldkv, dO, lse, delta, dk_out,
+                              ldo, Sq, Skv, H, D, sl2, scale, nsplit, part);
 }
 
 // ------------------------------------------------------ backward dK, dV at head dim 128: one wave per SIMD
@@ -1057,10 +1076,10 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_h128(const bf16_t* __rest
 // ------------------------------------------------------------------------------ backward dQ
 
 // NW waves (32 queries each) per workgroup share the K / V tiles.
-template <int HD, int NW, bool SPLIT>
 // Queries: Sq rows of q (stride ldq); keys: Skv rows of kv (stride ldkv, kv_elems addressable
 // elements, values D columns on); dQ to dq_out (stride ldo).
-__global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_bwd_dq_mfma(const bf16_t* __restrict__ q, int ldq,
+template <int HD, int NW, bool SPLIT>
+SR_DEV void attn_bwd_dq(const TileId id, int nB, bf16_t* smem, const bf16_t* __restrict__ q, int ldq,
                                                         const bf16_t* __restrict__ kv, int ldkv, uint32_t kv_elems,
                                                         const bf16_t* __restrict__ dO,
                                                         const float* __restrict__ lse, const float* __restrict__ delta,
@@ -1068,9 +1087,7 @@ __global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_bwd_dq_mfma(co
                                                         int D, float sl2, float scale, int nsplit, AttnPart part) {
   using G = Geo<HD>;
   constexpr int TE = G::TE, TB = G::TB, SGB = G::SGB, KS = G::KS, DB = G::DB;
-  __shared__ __attribute__((aligned(16))) bf16_t smem[NSTG * 2 * TE];   // stage: K tile, V tile
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, l32 = lane & 31, h32 = lane >> 5;
-  const TileId id = xcd_tile_id();
   const int b = id.b, hh = id.h;
   const bf16_t* qp = q + (size_t)b * Sq * ldq + hh * HD;
   const bf16_t* dop = dO + (size_t)b * Sq * D + hh * HD;
@@ -1209,6 +1226,18 @@ __global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_bwd_dq_mfma(co
   stage_t<HD>(smem, dq, scale, wid, lane);
   __syncthreads();
   unstage<HD, NW>(smem, dq_out + (size_t)b * Sq * ldo + hh * HD, ldo, run.blk * (32 * NW), Sq);
+}
+
+template <int HD, int NW, bool SPLIT>
+__global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_bwd_dq_mfma(const bf16_t* __restrict__ q, int ldq,
+                                                        const bf16_t* __restrict__ kv, int ldkv, uint32_t kv_elems,
+                                                        const bf16_t* __restrict__ dO,
+                                                        const float* __restrict__ lse, const float* __restrict__ delta,
+                                                        bf16_t* __restrict__ dq_out, int ldo, int Sq, int Skv, int H,
+                                                        int D, float sl2, float scale, int nsplit, AttnPart part) {
+  __shared__ __attribute__((aligned(16))) bf16_t smem[kBwdStage<HD>];
+  attn_bwd_dq<HD, NW, SPLIT>(xcd_tile_id(), gridDim.z, smem, q, ldq, kv, ldkv, kv_elems, dO, lse, delta, dq_out, ldo,
+                             Sq, Skv, H, D, sl2, scale, nsplit, part);
 }
 
 // ------------------------------------------------------------ backward dQ at head dim 128: one wave per SIMD
@@ -1837,6 +1866,31 @@ __global__ __launch_bounds__(256) void attn_combine_bwd(AttnPart part, int nspli
   reinterpret_cast<i32x2*>(dqkv)[i] = out;
 }
 
+// dK/dV and dQ of self-attention in one launch (qkv and dqkv token-major with row stride 3 D): the first
+// half of the grid's z range forms dK and dV, the second dQ, which needs nothing of the first.  Only where
+// one of them leaves half of the CUs idle, so that they run side by side: 8 samples of 128 tokens, 16 heads
+// (128 workgroups each), the step of 8 blocks 1898 -> 1855 us.  On grids that fill the chip the two launches
+// stay apart: one after the other their workgroups share operands in L2 and the second stream's kernels fall
+// into the gap (16 heads of 4050 tokens, 12 blocks 9420 -> 9670 us in one launch; four heads of 32 in four
+// runs 442 -> 464).
+template <int HD, int NW>
+__global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_bwd_self_mfma(
+    const bf16_t* __restrict__ qkv, uint32_t elems, const bf16_t* __restrict__ dO, const float* __restrict__ lse,
+    const float* __restrict__ delta, bf16_t* __restrict__ dqkv, int S, int H, int D, float sl2,
+    float scale) {
+  __shared__ __attribute__((aligned(16))) bf16_t smem[kBwdStage<HD>];
+  __shared__ __attribute__((aligned(16))) float fsm[kBwdRows];
+  const int nB = gridDim.z / 2, half = (int)blockIdx.z >= nB;
+  const int l = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * (blockIdx.z - half * nB));
+  const TileId id = xcd_tile_id(l, gridDim.x, gridDim.y, nB);
+  if (!half)
+    attn_bwd_dkv<HD, NW, false>(id, nB, smem, fsm, qkv, 3 * D, elems, qkv + D, 3 * D, dO, lse, delta, dqkv + D, 3 * D, S,
+                                S, H, D, sl2, scale, 1, AttnPart{});
+  else
+    attn_bwd_dq<HD, NW, false>(id, nB, smem, qkv, 3 * D, qkv + D, 3 * D, elems - D, dO, lse, delta, dqkv, 3 * D, S, S, H,
+                               D, sl2, scale, 1, AttnPart{});
+}
+
 // ------------------------------------------------------------------------- column sums
 // colsum[b,h,j] = sum over the S queries i of P[i,j], P = exp2(s * sl2 - lse) the forward's
 // probabilities: the attention token j receives in head h.  MFMA: the dK/dV kernel's score
@@ -2083,15 +2137,26 @@ static hipError_t bwd_mfma_hd(const bf16_t* qkv, const bf16_t* dO, const float* 
                               int B, int S, int H, int D, hipStream_t st, int nsplit, const AttnPart& part) {
   const double units = 2.0 * B * (double)S * S * D;   // one S x S x hd product over all heads
   const uint32_t all = (uint32_t)((size_t)B * S * 3 * D);
-  {
+  bool merged = false;
+  if constexpr (HD == 64) {   // timed calls keep the two passes' groups apart
+    constexpr int kw = attn_waves<HD>();
+    const dim3 g((unsigned)((S + 32 * kw - 1) / (32 * kw)), H, 2 * B);
+    merged = nsplit == 1 && (long)g.x * H * B <= 128 && !profiling();
+    if (merged)
+      SR_LAUNCH((attn_bwd_self_mfma<HD, kw>), g, dim3(64 * kw), 0, st, qkv, all, dO, lse, delta, dqkv, S, H, D,
+                attn_sl2(HD), 1.0f / sqrtf((float)HD));
+  }
+  if (!merged) {
     // algorithmic: dP, dV, dK (the recomputed scores are not counted)
     ProfScope ps("attn_bwd_dkv", 3 * units, (double)B * S * D * 2 * 6, st);
     SR_TRY_HIP(dkv_mfma_hd<HD>(qkv, 3 * D, all, qkv + D, 3 * D, dO, lse, delta, dqkv + D, 3 * D, B, S, S, H, D, st,
                                nsplit, part));
   }
-  ProfScope ps("attn_bwd_dq", units, (double)B * S * D * 2 * 5, st);
-  SR_TRY_HIP(dq_mfma_hd<HD>(qkv, 3 * D, qkv + D, 3 * D, all - D, dO, lse, delta, dqkv, 3 * D, B, S, S, H, D, st,
-                            nsplit, part));
+  if (!merged) {
+    ProfScope ps("attn_bwd_dq", units, (double)B * S * D * 2 * 5, st);
+    SR_TRY_HIP(dq_mfma_hd<HD>(qkv, 3 * D, qkv + D, 3 * D, all - D, dO, lse, delta, dqkv, 3 * D, B, S, S, H, D, st,
+                              nsplit, part));
+  }
   if (nsplit > 1) {
     const size_t n4 = (size_t)B * S * 3 * D / 4;
     SR_LAUNCH(attn_combine_bwd, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st, part, nsplit, dqkv, n4, D,
