@@ -135,16 +135,24 @@ SR_DEV int swz(int row) {
 template <int HD>
 SR_DEV int toff(int row, int chunk) { return row * HD + ((chunk ^ swz<HD>(row)) << 3); }
 
+// Buffer of `rows` rows of `ld` elements per sample (elems addressable from p) that ends with sample b.  A
+// sample's last tile may reach past its rows: into the next sample, whose values, were they not finite, would
+// spoil the products with the zeros that stand for the missing rows (0 x NaN).  Past the end of a buffer a load
+// returns zero, so the rows cost no test in the loop.  p may point some columns into the rows: the next sample's
+// first row then starts at or past the end as well.
+template <typename T>
+SR_DEV __amdgpu_buffer_rsrc_t sample_rsrc(const T* p, uint32_t elems, int b, int rows, int ld) {
+  const size_t end = (size_t)(b + 1) * rows * ld;
+  return make_rsrc(p, (uint32_t)((end < elems ? end : elems) * sizeof(T)));
+}
+
 // Rows r0..r0+63 of one head (columns base.. of a row-major tensor with row length ld)
 // into the LDS tile dst: HD / 8 blocks of 1 KB (64 / (HD / 8) rows each); lane l lands at
 // byte 16 l of its block, so it fetches the chunk that the swizzle places there.  Rows past
-// the sample's S tokens are read without a guard: they belong to the next sample (finite
-// values the callers mask) or lie past the tensor, where the buffer load returns zero; at head
-// dim 32 rows at or past `rows` read as zero, so a non-finite neighbouring sample stays out.
+// the sample's last one read as zero: rs ends with the sample (sample_rsrc).
 // NW waves share the blocks.
 template <int HD, int NW>
-SR_DEV void tile_load(__amdgpu_buffer_rsrc_t rs, uint32_t base, uint32_t ld, int r0, int rows, bf16_t* dst,
-                      bool valid = true) {
+SR_DEV void tile_load(__amdgpu_buffer_rsrc_t rs, uint32_t base, uint32_t ld, int r0, bf16_t* dst, bool valid = true) {
   using G = Geo<HD>;
   static_assert(G::BLK % NW == 0, "tile blocks per wave");
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
@@ -157,7 +165,7 @@ SR_DEV void tile_load(__amdgpu_buffer_rsrc_t rs, uint32_t base, uint32_t ld, int
     uint32_t off = base + ((uint32_t)(r0 + row) * ld + (uint32_t)c * 8u) * 2u;
     // a load past the last tile keeps the number of loads in flight uniform: it reads beyond
     // every tensor's extent (2 GiB at most), which returns zeros without a memory access
-    if (!valid || (HD == 32 && r0 + row >= rows)) off = 0x80000000u;
+    if (!valid) off = 0x80000000u;
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t*)(dst + blk * 512), 16, off, 0, 0, 0);
   }
 }
@@ -326,7 +334,7 @@ __global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_fwd_mfma(const
   const Run run = run_of<SPLIT>(id.blk, nsplit, nt);
   const int myq = run.blk * (32 * NW) + wid * 32 + l32;
   const bool ragged = Skv % KT != 0;
-  const __amdgpu_buffer_rsrc_t rq = make_rsrc(kv, kv_elems * 2u);
+  const __amdgpu_buffer_rsrc_t rq = sample_rsrc(kv, kv_elems, b, Skv, ldkv);
   const uint32_t kbase = (uint32_t)(((size_t)b * Skv * ldkv + hh * HD) * 2);
   const uint32_t vbase = kbase + (uint32_t)D * 2u;
   RowAddr<HD> ra;
@@ -340,8 +348,8 @@ __global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_fwd_mfma(const
 
   constexpr int kLoads = 2 * (G::BLK / NW);   // buffer loads per thread per tile (two tiles)
   auto load = [&](int t, int s) {
-    tile_load<HD, NW>(rq, kbase, (uint32_t)ldkv, t * KT, Skv, smem + s * 2 * TE, t < run.t1);
-    tile_load<HD, NW>(rq, vbase, (uint32_t)ldkv, t * KT, Skv, smem + s * 2 * TE + TE, t < run.t1);
+    tile_load<HD, NW>(rq, kbase, (uint32_t)ldkv, t * KT, smem + s * 2 * TE, t < run.t1);
+    tile_load<HD, NW>(rq, vbase, (uint32_t)ldkv, t * KT, smem + s * 2 * TE + TE, t < run.t1);
   };
   auto mask = [&](f32x16& sc, int k0) {   // keys past Skv do not exist
 #pragma unroll
@@ -546,16 +554,16 @@ SR_DEV void attn_bwd_dkv(const TileId id, int nB, bf16_t* smem, float* fsm, cons
 #pragma unroll
   for (int db = 0; db < DB; ++db) { zero16(dv[db]); zero16(dk[db]); }
 
-  const __amdgpu_buffer_rsrc_t rq = make_rsrc(q, q_elems * 2u);
-  const __amdgpu_buffer_rsrc_t rd = make_rsrc(dO, (uint32_t)((size_t)nB * Sq * D * 2));
-  const __amdgpu_buffer_rsrc_t rl = make_rsrc(lse, (uint32_t)((size_t)nB * H * Sq * 4));
-  const __amdgpu_buffer_rsrc_t rdl = make_rsrc(delta, (uint32_t)((size_t)nB * H * Sq * 4));
+  const __amdgpu_buffer_rsrc_t rq = sample_rsrc(q, q_elems, b, Sq, ldq);
+  const __amdgpu_buffer_rsrc_t rd = sample_rsrc(dO, (uint32_t)((size_t)nB * Sq * D), b, Sq, D);
+  const __amdgpu_buffer_rsrc_t rl = sample_rsrc(lse, (uint32_t)((size_t)nB * H * Sq), b, H, Sq);
+  const __amdgpu_buffer_rsrc_t rdl = sample_rsrc(delta, (uint32_t)((size_t)nB * H * Sq), b, H, Sq);
   const uint32_t qbase = (uint32_t)(((size_t)b * Sq * ldq + hh * HD) * 2);
   const uint32_t dbase = (uint32_t)(((size_t)b * Sq * D + hh * HD) * 2);
   const uint32_t lbase = (uint32_t)(((size_t)b * H + hh) * Sq * 4);
   auto load = [&](int t, int s) {
-    tile_load<HD, NW>(rq, qbase, (uint32_t)ldq, t * KT, Sq, smem + s * 2 * TE);
-    tile_load<HD, NW>(rd, dbase, (uint32_t)D, t * KT, Sq, smem + s * 2 * TE + TE);
+    tile_load<HD, NW>(rq, qbase, (uint32_t)ldq, t * KT, smem + s * 2 * TE);
+    tile_load<HD, NW>(rd, dbase, (uint32_t)D, t * KT, smem + s * 2 * TE + TE);
     const uint32_t lo = lbase + (uint32_t)(t * KT + lane) * 4u;
     if (wid == 0) __builtin_amdgcn_raw_ptr_buffer_load_lds(rl, (lds_ptr_t*)(fsm + s * 2 * KT), 4, lo, 0, 0, 0);
     if (wid == 1) __builtin_amdgcn_raw_ptr_buffer_load_lds(rdl, (lds_ptr_t*)(fsm + s * 2 * KT + KT), 4, lo, 0, 0, 0);
@@ -816,10 +824,10 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_h128(const bf16_t* __rest
   static_for<DB>([&](auto d) { pin_a(dv[d.value]); pin_a(dk[d.value]); });
   asm volatile("s_nop 7" ::: "memory");   // AGPR writes before the first MFMA reads
 
-  const __amdgpu_buffer_rsrc_t rq = make_rsrc(q, q_elems * 2u);
-  const __amdgpu_buffer_rsrc_t rd = make_rsrc(dO, (uint32_t)((size_t)gridDim.z * Sq * D * 2));
-  const __amdgpu_buffer_rsrc_t rl = make_rsrc(lse, (uint32_t)((size_t)gridDim.z * H * Sq * 4));
-  const __amdgpu_buffer_rsrc_t rdl = make_rsrc(delta, (uint32_t)((size_t)gridDim.z * H * Sq * 4));
+  const __amdgpu_buffer_rsrc_t rq = sample_rsrc(q, q_elems, b, Sq, ldq);
+  const __amdgpu_buffer_rsrc_t rd = sample_rsrc(dO, (uint32_t)((size_t)gridDim.z * Sq * D), b, Sq, D);
+  const __amdgpu_buffer_rsrc_t rl = sample_rsrc(lse, (uint32_t)((size_t)gridDim.z * H * Sq), b, H, Sq);
+  const __amdgpu_buffer_rsrc_t rdl = sample_rsrc(delta, (uint32_t)((size_t)gridDim.z * H * Sq), b, H, Sq);
   const uint32_t qbase = (uint32_t)(((size_t)b * Sq * ldq + hh * HD) * 2);
   const uint32_t dbase = (uint32_t)(((size_t)b * Sq * D + hh * HD) * 2);
   const uint32_t lbase = (uint32_t)(((size_t)b * H + hh) * Sq * 4);
@@ -828,8 +836,8 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_h128(const bf16_t* __rest
   // that every wave has LPT loads per tile in flight
   auto fill = [&](int t, int s) __attribute__((always_inline)) {
     const bool valid = t < nt;
-    tile_load<HD, NW>(rq, qbase, (uint32_t)ldq, t * KT, Sq, smem + s * TE, valid);
-    tile_load<HD, NW>(rd, dbase, (uint32_t)D, t * KT, Sq, smem + NST * TE + s * TE, valid);
+    tile_load<HD, NW>(rq, qbase, (uint32_t)ldq, t * KT, smem + s * TE, valid);
+    tile_load<HD, NW>(rd, dbase, (uint32_t)D, t * KT, smem + NST * TE + s * TE, valid);
     const uint32_t lo = valid ? lbase + (uint32_t)(t * KT + lane) * 4u : 0x80000000u;
     if (wid == 0) __builtin_amdgcn_raw_ptr_buffer_load_lds(rl, (lds_ptr_t*)(fsm + s * 2 * KT), 4, lo, 0, 0, 0);
     else if (wid == 1) __builtin_amdgcn_raw_ptr_buffer_load_lds(rdl, (lds_ptr_t*)(fsm + s * 2 * KT + KT), 4, lo, 0, 0, 0);
@@ -1113,7 +1121,7 @@ SR_DEV void attn_bwd_dq(const TileId id, int nB, bf16_t* smem, const bf16_t* __r
 #pragma unroll
   for (int db = 0; db < DB; ++db) zero16(dq[db]);
 
-  const __amdgpu_buffer_rsrc_t rq = make_rsrc(kv, kv_elems * 2u);
+  const __amdgpu_buffer_rsrc_t rq = sample_rsrc(kv, kv_elems, b, Skv, ldkv);
   const uint32_t kbase = (uint32_t)(((size_t)b * Skv * ldkv + hh * HD) * 2);
   const uint32_t vbase = kbase + (uint32_t)D * 2u;
   RowAddr<HD> ra;
@@ -1122,8 +1130,8 @@ SR_DEV void attn_bwd_dq(const TileId id, int nB, bf16_t* smem, const bf16_t* __r
   ta.init(lds_addr(smem), lane);
   constexpr int kLoads = 2 * (G::BLK / NW);   // buffer loads per thread per tile (two tiles)
   auto load = [&](int t, int s) {
-    tile_load<HD, NW>(rq, kbase, (uint32_t)ldkv, t * KT, Skv, smem + s * 2 * TE, t < run.t1);
-    tile_load<HD, NW>(rq, vbase, (uint32_t)ldkv, t * KT, Skv, smem + s * 2 * TE + TE, t < run.t1);
+    tile_load<HD, NW>(rq, kbase, (uint32_t)ldkv, t * KT, smem + s * 2 * TE, t < run.t1);
+    tile_load<HD, NW>(rq, vbase, (uint32_t)ldkv, t * KT, smem + s * 2 * TE + TE, t < run.t1);
   };
   // K (tile 0) or V (tile 1) row fragments of key unit U of stage SG
   auto read_rows = [&](auto sg, auto uu, auto tl, RawFrag<true> (&fr)[KS]) {
@@ -1317,13 +1325,13 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dq_h128(const bf16_t* __restr
   static_for<DB>([&](auto d) { pin_a(dq[d.value]); });
   asm volatile("s_nop 7" ::: "memory");   // AGPR writes before the first MFMA reads
 
-  const __amdgpu_buffer_rsrc_t rkv = make_rsrc(kv, kv_elems * 2u);
+  const __amdgpu_buffer_rsrc_t rkv = sample_rsrc(kv, kv_elems, b, Skv, ldkv);
   const uint32_t kbase = (uint32_t)(((size_t)b * Skv * ldkv + hh * HD) * 2);
   const uint32_t vbase = kbase + (uint32_t)D * 2u;
   auto fill = [&](int t, int s) __attribute__((always_inline)) {
     const bool valid = t < nt;
-    tile_load<HD, NW>(rkv, kbase, (uint32_t)ldkv, t * KT, Skv, smem + s * TE, valid);
-    tile_load<HD, NW>(rkv, vbase, (uint32_t)ldkv, t * KT, Skv, smem + NST * TE + s * TE, valid);
+    tile_load<HD, NW>(rkv, kbase, (uint32_t)ldkv, t * KT, smem + s * TE, valid);
+    tile_load<HD, NW>(rkv, vbase, (uint32_t)ldkv, t * KT, smem + NST * TE + s * TE, valid);
   };
 
   const uint32_t sbase = lds_addr(smem);
@@ -1578,13 +1586,13 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_h128(const bf16_t* __restrict
   asm volatile("s_nop 7" ::: "memory");
   float m_run = -INFINITY;   // running reference max of the raw scores
 
-  const __amdgpu_buffer_rsrc_t rkv = make_rsrc(kv, kv_elems * 2u);
+  const __amdgpu_buffer_rsrc_t rkv = sample_rsrc(kv, kv_elems, b, Skv, ldkv);
   const uint32_t kbase = (uint32_t)(((size_t)b * Skv * ldkv + hh * HD) * 2);
   const uint32_t vbase = kbase + (uint32_t)D * 2u;
   auto fill = [&](int t, int s) __attribute__((always_inline)) {
     const bool valid = t < nt;
-    tile_load<HD, NW>(rkv, kbase, (uint32_t)ldkv, t * KT, Skv, smem + s * TE, valid);
-    tile_load<HD, NW>(rkv, vbase, (uint32_t)ldkv, t * KT, Skv, smem + NST * TE + s * TE, valid);
+    tile_load<HD, NW>(rkv, kbase, (uint32_t)ldkv, t * KT, smem + s * TE, valid);
+    tile_load<HD, NW>(rkv, vbase, (uint32_t)ldkv, t * KT, smem + NST * TE + s * TE, valid);
   };
   const uint32_t sbase = lds_addr(smem);
   uint32_t ra[KS];
@@ -1919,12 +1927,12 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_colsum_mfma(const bf16_t
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) kf[ks] = mykey < S ? ld8(kp + (size_t)mykey * ld + ks * 16 + 8 * h32) : zero8();
 
-  const __amdgpu_buffer_rsrc_t rq = make_rsrc(qkv, (uint32_t)((size_t)gridDim.z * S * ld * 2));
-  const __amdgpu_buffer_rsrc_t rl = make_rsrc(lse, (uint32_t)((size_t)gridDim.z * H * S * 4));
+  const __amdgpu_buffer_rsrc_t rq = sample_rsrc(qkv, (uint32_t)((size_t)gridDim.z * S * ld), b, S, (int)ld);
+  const __amdgpu_buffer_rsrc_t rl = sample_rsrc(lse, (uint32_t)((size_t)gridDim.z * H * S), b, H, S);
   const uint32_t qbase = (uint32_t)(((size_t)b * S * ld + hh * HD) * 2);
   const uint32_t lbase = (uint32_t)(((size_t)b * H + hh) * S * 4);
   auto load = [&](int t, int s) {
-    tile_load<HD, NW>(rq, qbase, (uint32_t)ld, t * KT, S, smem + s * TE);
+    tile_load<HD, NW>(rq, qbase, (uint32_t)ld, t * KT, smem + s * TE);
     const uint32_t lo = lbase + (uint32_t)(t * KT + lane) * 4u;
     if (wid == 0) __builtin_amdgcn_raw_ptr_buffer_load_lds(rl, (lds_ptr_t*)(fsm + s * KT), 4, lo, 0, 0, 0);
   };
