@@ -136,7 +136,8 @@ SR_API const char* sr_last_error(void);
 SR_API const char* sr_version(void);
 
 /* Bytes of the `saved` (activations kept from forward for backward) and
- * `scratch` buffers needed by the block calls at S tokens per sample. */
+ * `scratch` buffers needed by the block calls at S tokens per sample.  Neither falls when S or B
+ * grows, all else equal: buffers sized for the largest call serve the smaller ones. */
 SR_API sr_status sr_workspace_bytes(const sr_config* cfg, int32_t S, size_t* saved_bytes,
                              size_t* scratch_bytes);
 
@@ -289,7 +290,8 @@ typedef struct {
 } sr_edm_block_grads;
 
 /* Bytes of `saved` and `scratch` for the generative blocks at S query tokens per sample and
- * cfg->L conditioning tokens (cfg->kind and cfg->idx_shared are not used). */
+ * cfg->L conditioning tokens (cfg->kind and cfg->idx_shared are not used); as above, neither falls
+ * when S or B grows. */
 SR_API sr_status sr_edm_workspace_bytes(const sr_config* cfg, int32_t S, size_t* saved_bytes,
                                  size_t* scratch_bytes);
 

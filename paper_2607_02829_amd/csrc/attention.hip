@@ -2025,15 +2025,29 @@ static inline float attn_sl2(int hd) { return 1.4426950408889634f / sqrtf((float
 // dK/dV 112 -> 46, dQ 81 -> 32, combination 9 us; four heads of 32 (128 workgroups, four runs) 59 ->
 // 35, 94 -> 46, 60 -> 29, 9 us.
 // At head dim 128 the register-explicit kernels stay uncut (their models have eight heads or more).
+static int split_rows(int hd) { return 32 * (hd == 64 ? attn_waves<64>() : attn_waves<32>()); }
+static int split_workgroups(int hd) { return hd == 64 ? 256 : 512; }   // one round of them
+constexpr int kRunTiles = 8;
+
 int attn_splits(int dtype, int B, int S, int H, int hd, int cap) {
   if (dtype != kBF16 || hd == 128) return 1;
-  const int rows = 32 * (hd == 64 ? attn_waves<64>() : attn_waves<32>());
+  const int rows = split_rows(hd);
   const long wgs = (long)((S + rows - 1) / rows) * H * B;
   const int nt = (S + KT - 1) / KT;
-  const int n = (int)std::min<long>(std::min(cap, kMaxSplit), std::min<long>((hd == 64 ? 256 : 512) / wgs, nt / 8));
+  const int n = (int)std::min<long>(std::min(cap, kMaxSplit), std::min<long>(split_workgroups(hd) / wgs, nt / kRunTiles));
   if (n < 2) return 1;
   const int per = (nt + n - 1) / n;
   return (nt + per - 1) / per;   // no empty run
+}
+
+// n runs need n kRunTiles tiles in a sample and at most 1 / n of a round of workgroups in the call.
+size_t attn_split_rows(int dtype, int B, int S, int H, int hd) {
+  if (dtype != kBF16 || hd == 128) return 0;
+  size_t most = 0;
+  for (int n = 2; n <= kMaxSplit; ++n)
+    if ((S + KT - 1) / KT >= n * kRunTiles)
+      most = std::max(most, n * std::min((size_t)B * S, (size_t)split_rows(hd) * (split_workgroups(hd) / n / H)));
+  return most;
 }
 
 // The MFMA kernels on Sq query rows and Skv key/value rows (self-attention: both S, q, k and v

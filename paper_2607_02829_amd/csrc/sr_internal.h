@@ -189,6 +189,9 @@ struct AttnPart {
   float* ml = nullptr;
 };
 int attn_splits(int dtype, int B, int S, int H, int hd, int cap);
+// The most rows, over all its runs together, of any call of up to B samples of up to S tokens that is cut: what
+// its planes take (at most 50 MB of fp32 qkv rows).
+size_t attn_split_rows(int dtype, int B, int S, int H, int hd);
 hipError_t launch_attn_fwd(int dtype, const void* qkv, void* O, float* lse, int B, int S, int H, int D,
                            hipStream_t st, int nsplit = 1, const AttnPart& part = {});
 hipError_t launch_attn_colsum(int dtype, const void* qkv, const float* lse, float* colsum, int B, int S, int H, int D,

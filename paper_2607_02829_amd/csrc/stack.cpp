@@ -139,9 +139,12 @@ size_t layout_scratch(const Dims& d, char* base, Scratch* out) {
   // recomputed operands of the weight-gradient GEMMs (written and read on the second stream)
   s.u_rc = c.take<void>(M * D * e);
   s.gz_rc = c.take<void>(M * F * e);
+  // Planes of a cut attention backward.  How many runs a call has does not grow with its tokens, so their room
+  // is that of the call with the most rows in runs up to this size: a scratch buffer serves every smaller call.
   s.attn_splits = attn_splits(d.dtype, d.B, d.S, d.H, d.D / d.H, kMaxSplit);
-  if (s.attn_splits > 1)   // at most 256 workgroups' rows: 50 MB
-    for (int k = 0; k < s.attn_splits; ++k) s.attn.p[k] = c.take<float>(M * 3 * D * 4);
+  float* planes = c.take<float>(attn_split_rows(d.dtype, d.B, d.S, d.H, d.D / d.H) * 3 * D * 4);
+  if (s.attn_splits > 1 && planes)
+    for (int k = 0; k < s.attn_splits; ++k) s.attn.p[k] = planes + k * M * 3 * D;
   if (out) *out = s;
   return c.off;
 }

@@ -52,6 +52,26 @@ def test_workspace_sizes_scale_with_tokens():
     assert s2 - 2 * (s3 - s2) >= 2 * 100 * (256 + 1024) * 2   # plus the shared temporaries
 
 
+@pytest.mark.parametrize("D,H", [(64, 1), (128, 4), (256, 4), (320, 5), (1024, 16), (256, 2)])
+def test_workspace_sizes_never_fall(D, H):
+    # a program allocates once, for its largest keep ratio and its largest batch, and then runs smaller calls
+    _lib_or_skip()
+    for query in (abi.sr_workspace_bytes, abi.sr_edm_workspace_bytes):
+        for B in (1, 3):
+            last = (0, 0)
+            cfg = _cfg(B=B, L=16384, D=D, H=H, F=4 * D, n_blocks=1)
+            for S in range(64, 16385):
+                got = query(cfg, S)
+                assert got[0] >= last[0] and got[1] >= last[1], (query.__name__, B, S, last, got)
+                last = got
+        for S in range(64, 4096, 31):
+            last = (0, 0)
+            for B in range(1, 17):
+                got = query(_cfg(B=B, L=4096, D=D, H=H, F=4 * D, n_blocks=1), S)
+                assert got[0] >= last[0] and got[1] >= last[1], (query.__name__, B, S, last, got)
+                last = got
+
+
 def test_stack_buffer_limit_counts_the_calls_rows():
     # 0.25 deg shape at B = 16: the routed stack's K = 4050 rows per sample stay below the 2 GiB
     # of its fp32 buffers (16 x 4050 x 4096 x 4 bytes), the dense one's L = 16200 rows do not
