@@ -48,10 +48,11 @@ constexpr int NSTG = 3;      // LDS stages
 // head dim 64).
 template <int HD>
 constexpr int attn_waves() { return HD == 64 ? 8 : 4; }
-// At head dim 32 the vector work of a score (the exponential, the split of P into two bf16 parts,
+// At head dim 32 the vector work of a score (the exponential, the split of P into three bf16 parts,
 // see split8) outweighs its MFMAs, registers are few, and the small models that use it have few
 // heads: four waves (128 rows) per workgroup, so that more CUs get one.  4050 tokens, four heads:
-// forward 58.7, dK/dV 94.1, dQ 60.0 us, against 4219, 2419 and 2260 us for one thread per row.
+// forward 59, dK/dV 114, dQ 63 us, against 4219, 2419 and 2260 us for one thread per row.  (In two
+// parts, 2^-18 of P, 57, 96 and 59 us; the fp32 products that these replace held all of P.)
 // Waves per SIMD that the register allocation of the templates below leaves room for.
 constexpr int attn_occ(int hd, int nw) { return hd == 64 ? 8 / nw : 2; }
 
@@ -86,16 +87,31 @@ SR_DEV bf16x8 neg8(bf16x8 v) {
   return __builtin_bit_cast(bf16x8, w);
 }
 
-// Head dim 32: eight fp32 values as bf16 pairs hi + lo (relative error 2^-18), so that products
-// with bf16 operands on the matrix cores keep what the probabilities and score gradients hold
-// beyond 8 bits: twice the MFMAs of a contraction that is short at this head dim.  Measured
-// against fp64, outputs and gradients are as close as with fp32 probabilities.
-SR_DEV void split8(const float* p, bf16x8& hi, bf16x8& lo) {
+// Head dim 32: eight fp32 values as sums of three bf16 parts of 8 significant bits each, which is all 24 bits of
+// fp32, so that products with bf16 operands on the matrix cores see the probabilities and score gradients as fp32
+// (bf16 operands multiply exactly, sums are fp32): three times the MFMAs of a contraction that is short at this
+// head dim.  The first two parts are cut off, not rounded: the remainder keeps the sign and is exact.
+struct Split8 {
+  bf16x8 part[3];
+};
+SR_DEV Split8 split8(const float* p) {
+  Split8 s;
+  float r[8];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    hi[i] = (__bf16)p[i];
-    lo[i] = (__bf16)(p[i] - (float)hi[i]);
+  for (int i = 0; i < 8; ++i) r[i] = p[i];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    i32x4 w;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)   // the upper halves of two values
+      w[i] = __builtin_amdgcn_perm(__float_as_uint(r[2 * i + 1]), __float_as_uint(r[2 * i]), 0x07060302u);
+    s.part[k] = __builtin_bit_cast(bf16x8, w);
+    if (k < 2) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) r[i] -= __uint_as_float(__float_as_uint(r[i]) & 0xFFFF0000u);
+    }
   }
+  return s;
 }
 
 SR_DEV f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
@@ -363,7 +379,7 @@ __global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_fwd_mfma(const
   // softmax denominators on the matrix cores: a 32-row A operand whose row 0 is all ones turns
   // the P^T MFMA into the column sums of P^T, so lsum[0] of lane l32 (first half) is the sum of
   // the bf16 probabilities of query l32 (the values the PV product uses); every other element
-  // stays zero
+  // stays zero.  At head dim 32 lsum[0] of each half-wave sums its own keys in fp32.
   f32x16 lsum;
   zero16(lsum);
   bf16x8 ones;
@@ -416,8 +432,8 @@ __global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_fwd_mfma(const
       m_run = m_ref;
     }
     const float nm = -m_run * sl2;
-    bf16x8 pb0[2], pb1[2], pl0[2], pl1[2];   // pl: low parts at head dim 32
     if constexpr (HD == 32) {
+      Split8 ps0[2], ps1[2];
       float p0[16], p1[16];
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
@@ -426,36 +442,46 @@ __global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_fwd_mfma(const
       }
 #pragma unroll
       for (int kk = 0; kk < 2; ++kk) {
-        split8(p0 + 8 * kk, pb0[kk], pl0[kk]);
-        split8(p1 + 8 * kk, pb1[kk], pl1[kk]);
-        lsum = mfma(ones, pl0[kk], lsum);
-        lsum = mfma(ones, pl1[kk], lsum);
+        ps0[kk] = split8(p0 + 8 * kk);
+        ps1[kk] = split8(p1 + 8 * kk);
+      }
+      // the denominator of the lane's half of the keys: adds cost less than twelve more MFMAs (16200 tokens,
+      // eight heads: 956 -> 870 us)
+      float tsum = 0.f;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) tsum += p0[r] + p1[r];
+      lsum[0] += tsum;
+      lgkm_wait<0>();
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+        const bf16x8 v0 = vt0[0][kk].settle(), v1 = vt1[0][kk].settle();
+#pragma unroll
+        for (int k = 2; k >= 0; --k) {
+          o[0] = mfma(v0, ps0[kk].part[k], o[0]);
+          o[0] = mfma(v1, ps1[kk].part[k], o[0]);
+        }
       }
     } else {
+      bf16x8 pb0[2], pb1[2];
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         pb0[r >> 3][r & 7] = (__bf16)ex2(fmaf(sc0[r], sl2, nm));
         pb1[r >> 3][r & 7] = (__bf16)ex2(fmaf(sc1[r], sl2, nm));
       }
-    }
-#pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-      lsum = mfma(ones, pb0[kk], lsum);
-      lsum = mfma(ones, pb1[kk], lsum);
-    }
-    lgkm_wait<0>();
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
 #pragma unroll
       for (int kk = 0; kk < 2; ++kk) {
-        const bf16x8 v0 = vt0[db][kk].settle(), v1 = vt1[db][kk].settle();
-        o[db] = mfma(v0, pb0[kk], o[db]);
-        o[db] = mfma(v1, pb1[kk], o[db]);
-        if constexpr (HD == 32) {
-          o[db] = mfma(v0, pl0[kk], o[db]);
-          o[db] = mfma(v1, pl1[kk], o[db]);
-        }
+        lsum = mfma(ones, pb0[kk], lsum);
+        lsum = mfma(ones, pb1[kk], lsum);
       }
+      lgkm_wait<0>();
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+          o[db] = mfma(vt0[db][kk].settle(), pb0[kk], o[db]);
+          o[db] = mfma(vt1[db][kk].settle(), pb1[kk], o[db]);
+        }
+    }
   };
 
   load(run.t0, 0);
@@ -495,7 +521,7 @@ __global__ __launch_bounds__(64 * NW, attn_occ(HD, NW)) void attn_fwd_mfma(const
 
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();   // every wave is done with the stages before they hold the output
-  const float l_tot = half_pair_sum(lsum[0]);   // the second half's element is zero
+  const float l_tot = half_pair_sum(lsum[0]);   // the second half's element is zero (head dim 64)
   if constexpr (SPLIT) {   // unnormalised O, its reference max and denominator
     if (myq < Sq) {
       store_part<HD>(part.p[run.sp] + ((size_t)b * Sq + myq) * D + hh * HD, o, h32);
@@ -593,7 +619,8 @@ SR_DEV void attn_bwd_dkv(const TileId id, int nB, bf16_t* smem, float* fsm, cons
     f32x16 dpv;
     dp_of(s, u, dpv);
     const float* ls = fsm + s * 2 * KT + u * 32;
-    bf16x8 pb[2], sb[2], pl[2], sl[2];   // pl, sl: low parts at head dim 32
+    bf16x8 pb[2], sb[2];
+    Split8 ps[2], ss[2];   // P and dS at head dim 32
     float pf[HD == 32 ? 16 : 1], sf[HD == 32 ? 16 : 1];
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -614,8 +641,8 @@ SR_DEV void attn_bwd_dkv(const TileId id, int nB, bf16_t* smem, float* fsm, cons
     if constexpr (HD == 32) {
 #pragma unroll
       for (int kk = 0; kk < 2; ++kk) {
-        split8(pf + 8 * kk, pb[kk], pl[kk]);
-        split8(sf + 8 * kk, sb[kk], sl[kk]);
+        ps[kk] = split8(pf + 8 * kk);
+        ss[kk] = split8(sf + 8 * kk);
       }
     }
     // keep the transposed fragment reads after the arithmetic: hoisted above it they hold
@@ -628,12 +655,16 @@ SR_DEV void attn_bwd_dkv(const TileId id, int nB, bf16_t* smem, float* fsm, cons
 #pragma unroll
       for (int kk = 0; kk < 2; ++kk) {
         const bf16x8 dof = tr_frag<HD>(dOs, u * 32 + kk * 16, db * 32);
-        dv[db] = mfma(dof, pb[kk], dv[db]);
         const bf16x8 qfr = tr_frag<HD>(Qs, u * 32 + kk * 16, db * 32);
-        dk[db] = mfma(qfr, sb[kk], dk[db]);
         if constexpr (HD == 32) {
-          dv[db] = mfma(dof, pl[kk], dv[db]);
-          dk[db] = mfma(qfr, sl[kk], dk[db]);
+#pragma unroll
+          for (int k = 2; k >= 0; --k) {
+            dv[db] = mfma(dof, ps[kk].part[k], dv[db]);
+            dk[db] = mfma(qfr, ss[kk].part[k], dk[db]);
+          }
+        } else {
+          dv[db] = mfma(dof, pb[kk], dv[db]);
+          dk[db] = mfma(qfr, sb[kk], dk[db]);
         }
       }
   };
@@ -1158,7 +1189,8 @@ SR_DEV void attn_bwd_dq(const TileId id, int nB, bf16_t* smem, const bf16_t* __r
         ta.template read<SG * SGB, U * 32 + decltype(kk)::value * 16, decltype(db)::value>(fk[db.value][kk.value]);
       });
     });
-    bf16x8 sb[2], sl[2];   // sl: low parts at head dim 32
+    bf16x8 sb[2];
+    Split8 ss[2];   // dS at head dim 32
     float sf[HD == 32 ? 16 : 1];
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -1172,7 +1204,7 @@ SR_DEV void attn_bwd_dq(const TileId id, int nB, bf16_t* smem, const bf16_t* __r
     }
     if constexpr (HD == 32) {
 #pragma unroll
-      for (int kk = 0; kk < 2; ++kk) split8(sf + 8 * kk, sb[kk], sl[kk]);
+      for (int kk = 0; kk < 2; ++kk) ss[kk] = split8(sf + 8 * kk);
     }
     lgkm_wait<0>();
 #pragma unroll
@@ -1180,8 +1212,12 @@ SR_DEV void attn_bwd_dq(const TileId id, int nB, bf16_t* smem, const bf16_t* __r
 #pragma unroll
       for (int kk = 0; kk < 2; ++kk) {
         const bf16x8 kt = fk[db][kk].settle();
-        dq[db] = mfma(kt, sb[kk], dq[db]);
-        if constexpr (HD == 32) dq[db] = mfma(kt, sl[kk], dq[db]);
+        if constexpr (HD == 32) {
+#pragma unroll
+          for (int k = 2; k >= 0; --k) dq[db] = mfma(kt, ss[kk].part[k], dq[db]);
+        } else {
+          dq[db] = mfma(kt, sb[kk], dq[db]);
+        }
       }
   };
 
@@ -2023,7 +2059,7 @@ static inline float attn_sl2(int hd) { return 1.4426950408889634f / sqrtf((float
 // of at least eight tiles: below that a run's start and the combination cost what the cut saves.
 // 4050 tokens, combination included: four heads of 64 (64 workgroups, four runs) forward 71 -> 33,
 // dK/dV 112 -> 46, dQ 81 -> 32, combination 9 us; four heads of 32 (128 workgroups, four runs) 59 ->
-// 35, 94 -> 46, 60 -> 29, 9 us.
+// 32, 114 -> 55, 63 -> 33, 9 us.
 // At head dim 128 the register-explicit kernels stay uncut (their models have eight heads or more).
 static int split_rows(int hd) { return 32 * (hd == 64 ? attn_waves<64>() : attn_waves<32>()); }
 static int split_workgroups(int hd) { return hd == 64 ? 256 : 512; }   // one round of them
