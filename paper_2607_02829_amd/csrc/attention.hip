@@ -2196,21 +2196,23 @@ static hipError_t bwd_mfma_hd(const bf16_t* qkv, const bf16_t* dO, const float* 
   const double units = 2.0 * B * (double)S * S * D;   // one S x S x hd product over all heads
   const uint32_t all = (uint32_t)((size_t)B * S * 3 * D);
   bool merged = false;
-  if constexpr (HD == 64) {   // timed calls keep the two passes' groups apart
+  if constexpr (HD == 64) {
     constexpr int kw = attn_waves<HD>();
     const dim3 g((unsigned)((S + 32 * kw - 1) / (32 * kw)), H, 2 * B);
-    merged = nsplit == 1 && (long)g.x * H * B <= 128 && !profiling();
-    if (merged)
+    merged = nsplit == 1 && (long)g.x * H * B <= 128;
+    if (merged) {   // timed as one group, of both passes' work
+      ProfScope ps("attn_bwd_dkv", 4 * units, (double)B * S * D * 2 * 11, st);
       SR_LAUNCH((attn_bwd_self_mfma<HD, kw>), g, dim3(64 * kw), 0, st, qkv, all, dO, lse, delta, dqkv, S, H, D,
                 attn_sl2(HD), 1.0f / sqrtf((float)HD));
+    }
   }
   if (!merged) {
-    // algorithmic: dP, dV, dK (the recomputed scores are not counted)
-    ProfScope ps("attn_bwd_dkv", 3 * units, (double)B * S * D * 2 * 6, st);
-    SR_TRY_HIP(dkv_mfma_hd<HD>(qkv, 3 * D, all, qkv + D, 3 * D, dO, lse, delta, dqkv + D, 3 * D, B, S, S, H, D, st,
-                               nsplit, part));
-  }
-  if (!merged) {
+    {
+      // algorithmic: dP, dV, dK (the recomputed scores are not counted)
+      ProfScope ps("attn_bwd_dkv", 3 * units, (double)B * S * D * 2 * 6, st);
+      SR_TRY_HIP(dkv_mfma_hd<HD>(qkv, 3 * D, all, qkv + D, 3 * D, dO, lse, delta, dqkv + D, 3 * D, B, S, S, H, D, st,
+                                 nsplit, part));
+    }
     ProfScope ps("attn_bwd_dq", units, (double)B * S * D * 2 * 5, st);
     SR_TRY_HIP(dq_mfma_hd<HD>(qkv, 3 * D, qkv + D, 3 * D, all - D, dO, lse, delta, dqkv, 3 * D, B, S, S, H, D, st,
                               nsplit, part));

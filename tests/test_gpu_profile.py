@@ -48,3 +48,14 @@ def test_timing_leaves_results_unchanged(case, name_filter):
         assert prof[name_filter]["ms"] > 0.0
     else:
         assert prof["attn_bwd_dkv"]["ms"] > 0.0 and prof["ln_bwd"]["ms"] > 0.0
+
+
+def test_timed_calls_run_the_same_kernels():
+    # few workgroups: the attention backward is one launch, timed as attn_bwd_dkv
+    w, nb, K, shared = CASES["bf16"]
+    abi.sr_profile_start("attn_bwd")
+    try:
+        _run(w, nb, K, shared, True)
+    finally:
+        prof = abi.sr_profile_stop()
+    assert set(prof) == {"attn_bwd_dkv"} and prof["attn_bwd_dkv"]["launches"] == nb, prof
