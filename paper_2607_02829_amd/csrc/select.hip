@@ -32,41 +32,70 @@ SR_DEV uint64_t mix64(uint64_t z) {
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / 64;
 
-// Writes the kept tokens of 0 .. L-1 to out in index order: those with lt(i), and of those with
-// eq(i) the need_eq of lowest index.  Each wave owns a contiguous run of tokens and counts it
+// Writes the kept tokens of 0 .. L-1 to out in index order: those of class kKeep, and of those of class kTie
+// the need_tie of lowest index.  Each wave owns a contiguous run of tokens and counts it
 // (ballots); one barrier shares the counts, then each wave writes its run.  (A block-wide scan
-// per 1024 tokens, two barriers each, made random selection of 4050 of 16200 tokens take 21.3 us
-// and top-k of 2048 of 8192 26.7 us; 16.3 and 19.5 with this and the histograms below.)
+// per 1024 tokens, two barriers each, made random selection of 4050 of 16200 tokens take 20.9 us
+// and top-k of 2048 of 8192 given scores 23.4 us; 15.1 and 14.0 with this and the histograms below.)
+// Keys in LDS are classified twice, to count and to write.  Keys that have to be formed again (a hash, a sum over
+// score planes) are classified once (KEEP): `keep` is LDS for the ballots of `groups` groups of 64 tokens, and the
+// tokens are taken in segments of that many groups.  65160 tokens, random 100 us with the block-wide scan, 81
+// classified twice, 70 classified once; top-k over 16 planes 308, 403, 208.
 // wsum: 2 kSelWaves ints of LDS.
-template <typename Lt, typename Eq>
-SR_DEV void compact(Lt lt, Eq eq, int L, int K, int need_eq, int* wsum, int32_t* out) {
+enum { kDrop = 0, kKeep = 1, kTie = 2 };
+template <bool KEEP, typename Cls>
+SR_DEV void compact(Cls cls, int L, int K, int need_tie, int* wsum, int32_t* out, uint64_t* keep, int groups) {
   const int lane = threadIdx.x & 63, wid = wave_index();
-  const int run = ((L + kSelWaves - 1) / kSelWaves + 63) & ~63;
-  const int i0 = wid * run, i1 = min(L, i0 + run);
   const uint64_t below = (1ull << lane) - 1ull;
-  int nlt = 0, neq = 0;
+  const int seg = KEEP ? groups * 64 : L;
+  int base0 = 0, ties0 = 0;   // kept and tied tokens of the segments before
+  int s0 = 0;
+  do {
+    const int n = KEEP ? min(seg, L - s0) : L;
+    const int run = ((n + kSelWaves - 1) / kSelWaves + 63) & ~63;
+    const int i0 = s0 + min(n, wid * run), i1 = s0 + min(n, (wid + 1) * run);
+    int nkeep = 0, ntie = 0;
 #pragma unroll 4
-  for (int i = i0; i < i1; i += 64) {
-    const int t = i + lane;
-    nlt += __popcll(__ballot(t < i1 && lt(t)));
-    neq += __popcll(__ballot(t < i1 && eq(t)));
-  }
-  if (lane == 0) { wsum[wid] = nlt; wsum[kSelWaves + wid] = neq; }
-  __syncthreads();
-  int base = 0, eqs = 0;   // tokens with lt and with eq in the runs before this one
-  for (int w = 0; w < wid; ++w) { base += wsum[w]; eqs += wsum[kSelWaves + w]; }
-  base += min(eqs, need_eq);
-  for (int i = i0; i < i1; i += 64) {
-    const int t = i + lane;
-    const bool e = t < i1 && eq(t);
-    const uint64_t me = __ballot(e);
-    const bool f = (t < i1 && lt(t)) || (e && eqs + __popcll(me & below) < need_eq);
-    const uint64_t mf = __ballot(f);
-    const int pos = base + __popcll(mf & below);
-    if (f && pos < K) out[pos] = t;
-    base += __popcll(mf);
-    eqs += __popcll(me);
-  }
+    for (int i = i0; i < i1; i += 64) {
+      const int t = i + lane;
+      const int c = t < i1 ? cls(t) : kDrop;
+      const uint64_t mk = __ballot(c == kKeep), mt = __ballot(c == kTie);
+      nkeep += __popcll(mk);
+      ntie += __popcll(mt);
+      if (KEEP && lane == 0) {
+        keep[(i - s0) / 32] = mk;
+        keep[(i - s0) / 32 + 1] = mt;
+      }
+    }
+    if (lane == 0) { wsum[wid] = nkeep; wsum[kSelWaves + wid] = ntie; }
+    __syncthreads();
+    int base = base0, ties = ties0;
+    for (int w = 0; w < wid; ++w) { base += wsum[w]; ties += wsum[kSelWaves + w]; }
+    if constexpr (KEEP)
+      for (int w = 0; w < kSelWaves; ++w) { base0 += wsum[w]; ties0 += wsum[kSelWaves + w]; }
+    base += min(ties, need_tie);
+    for (int i = i0; i < i1; i += 64) {
+      const int t = i + lane;
+      uint64_t mk, mt;
+      if constexpr (KEEP) {
+        mk = keep[(i - s0) / 32];
+        mt = keep[(i - s0) / 32 + 1];
+      } else {
+        const int c = t < i1 ? cls(t) : kDrop;
+        mk = __ballot(c == kKeep);
+        mt = __ballot(c == kTie);
+      }
+      const uint64_t me = 1ull << lane;
+      const bool f = (mk & me) || ((mt & me) && ties + __popcll(mt & below) < need_tie);
+      const uint64_t mf = __ballot(f);
+      const int pos = base + __popcll(mf & below);
+      if (f && pos < K) out[pos] = t;
+      base += __popcll(mf);
+      ties += __popcll(mt);
+    }
+    s0 += seg;
+    if constexpr (KEEP) __syncthreads();   // the counts and ballots before the next segment's
+  } while (KEEP && s0 < L);
 }
 
 // One radix pass: among keys with (key & mask) == prefix, histogram the digit at
@@ -149,8 +178,11 @@ __global__ __launch_bounds__(kSelThreads) void select_random_kernel(int L, int K
     if (radix_pass<1>(key_at, L, shift, prefix, mask, k, hist, sh)) break;
   // exactly K keys have (key & mask) <= prefix: the chosen bin is taken whole
 
-  compact([&](int i) { return (key_at(i) & mask) <= prefix; }, [](int) { return false; }, L, K, 0, wsum,
-          idx + (size_t)b * K);
+  int32_t* const out = idx + (size_t)b * K;
+  if (cached) compact<false>([&](int i) { return (kc[i] & mask) <= prefix ? kKeep : kDrop; }, L, K, 0, wsum, out, kc, 0);
+  else
+    compact<true>([&](int i) { return (key_of(i) & mask) <= prefix ? kKeep : kDrop; }, L, K, 0, wsum, out, kc,
+                  kSelCache / 2);
 }
 
 // ------------------------------------------------------------------------ top-k
@@ -192,7 +224,7 @@ constexpr int kTopkRep = 16;
 // order from +0 (one plane: the score itself).
 __global__ __launch_bounds__(kSelThreads) void select_topk_kernel(const float* __restrict__ score,
                                                                     int parts, int L, int K, int32_t* idx) {
-  __shared__ uint32_t kc[kTopkCache];
+  __shared__ __attribute__((aligned(8))) uint32_t kc[kTopkCache];
   __shared__ int hist[kTopkRep * 257 + 4];
   __shared__ uint64_t sh[3];
   __shared__ int wsum[2 * kSelWaves];
@@ -222,8 +254,11 @@ __global__ __launch_bounds__(kSelThreads) void select_topk_kernel(const float* _
   for (int shift = 24; shift >= 0; shift -= 8)
     if (radix_pass<kTopkRep>(key_of, L, shift, prefix, mask, k, hist, sh)) break;
   // kept: the keys whose top bits lie below the prefix, and the first k of those that share it
-  compact([&](int i) { return (key_of(i) & mask) < prefix; }, [&](int i) { return (key_of(i) & mask) == prefix; }, L,
-          K, k, wsum, idx + (size_t)b * K);
+  auto cls = [&](uint64_t key) { return key < prefix ? kKeep : key == prefix ? kTie : kDrop; };
+  int32_t* const out = idx + (size_t)b * K;
+  uint64_t* const keep = reinterpret_cast<uint64_t*>(kc);
+  if (cached) compact<false>([&](int i) { return cls(kc[i] & mask); }, L, K, k, wsum, out, keep, 0);
+  else compact<true>([&](int i) { return cls(key_from(i) & mask); }, L, K, k, wsum, out, keep, kTopkCache / 4);
 }
 
 // ------------------------------------------------------------------------ validation

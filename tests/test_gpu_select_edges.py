@@ -42,3 +42,26 @@ def test_topk_planes(L, K, kind):
     abi.sr_select_topk_scores(_cfg(L), K, planes, 1, idx)
     torch.cuda.synchronize()
     assert np.array_equal(idx.cpu().numpy(), osel.select_topk_planes(score, K))
+
+
+@pytest.mark.parametrize("L,K", [(638976, 159744), (638977, 160000), (1300001, 1299999)])
+def test_random_in_segments(L, K):
+    # keys not kept in LDS: their classes are, for 638976 tokens at a time
+    test_random(L, K)
+
+
+@pytest.mark.parametrize("L,K", [(32769, 8192), (524288, 131072), (524289, 400000), (1100003, 550000)])
+@pytest.mark.parametrize("parts", [1, 5])
+@pytest.mark.parametrize("kind", ["equal", "few", "random"])
+def test_topk_planes_in_segments(L, K, parts, kind):
+    # 524288 tokens at a time; ties on both sides of a segment's end
+    print(f"[select topk segments] L={L} K={K} parts={parts} {kind}", flush=True)
+    rng = np.random.default_rng(L + K)
+    shape = (2, parts, L)
+    score = {"equal": np.full(shape, 3.0, np.float32), "few": rng.integers(0, 3, shape).astype(np.float32),
+             "random": rng.random(shape, dtype=np.float32)}[kind]
+    planes = torch.from_numpy(score).cuda()
+    idx = torch.empty((2, K), dtype=torch.int32, device="cuda")
+    abi.sr_select_topk_scores(_cfg(L), K, planes, parts, idx)
+    torch.cuda.synchronize()
+    assert np.array_equal(idx.cpu().numpy(), osel.select_topk_planes(score, K))
