@@ -650,11 +650,11 @@ static hipError_t launch_reduce(const float* part, int splits, size_t n, float* 
 // 24.8; weight gradients 3072 x 1024 over 1024 tokens 19.5 -> 17.4, over 4050 43.1 -> 39.8.  Sixteen
 // waves, and tiles of 256 x 128 and 128 x 256, lie within 3 % of these or behind but for the 1024-column
 // products of 16200 tokens (153 against 164).
-// Two shapes stay at four waves (w4) where kernels of the two streams share the CUs and the second wave
-// per SIMD delays the other stream's more than it gains: weight gradients on 128 x 128 tiles over more
-// than 2048 tokens (adaLN step at 4096 tokens 804 -> 782 us, 12-block step at 4050 9350 -> 9330; at 1024
-// tokens eight are ahead, 1875 against 1895), and two workgroups per CU past two rounds of them (dense
-// block of 16200 tokens 6300 -> 6262; at 4050 tokens eight are ahead, 9350 against 9415).
+// The 128 x 128 tiles of the weight gradients stay at four waves (w4) over many tokens: these run beside the
+// other stream's kernels, which a second wave per SIMD on the shared CUs delays by more than it gains (dw_plan).
+// The forward and dX products gain nothing from it (12-block step at 4050 tokens 9330 with four waves past two
+// rounds of workgroups, 9319 with eight; dense block of 16200 tokens 6251, 6240; 8192 tokens of 768, two blocks, 3332,
+// 3300; medians of nine alternated runs that spread by 0.5 %).
 enum TileShape { T128x128x2, T128x128x2w4, T128x128, T128x128w4, T64x128, T64x64g2, T32x64g4, T32x32g8 };
 struct ShapeInfo {
   int bm, bn, occ;
@@ -694,13 +694,16 @@ static hipError_t run_shape(int shape, const GemmDesc& g, const EpiArgs& ep, int
   switch (shape) {
     case T128x128: return run_mfma_tile<128, 128, 2, 4, 1, 4, 1, EPI, T, Ta>(g, ep, splits, kps, st);
     case T128x128x2: return run_mfma_tile<128, 128, 2, 4, 1, 2, 2, EPI, T, Ta>(g, ep, splits, kps, st);
-    case T128x128x2w4: return run_mfma_tile<128, 128, 2, 2, 1, 2, 2, EPI, T, Ta>(g, ep, splits, kps, st);
     case T64x128: return run_mfma_tile<64, 128, 2, 4, 1, 4, 1, EPI, T, Ta>(g, ep, splits, kps, st);
     default: break;
   }
-  if constexpr (EPI == EPI_DW)
-    if (shape == T128x128w4) return run_mfma_tile<128, 128, 2, 2, 1, 4, 1, EPI, T, Ta>(g, ep, splits, kps, st);
-  if constexpr (EPI != EPI_DW) {
+  if constexpr (EPI == EPI_DW) {
+    switch (shape) {
+      case T128x128w4: return run_mfma_tile<128, 128, 2, 2, 1, 4, 1, EPI, T, Ta>(g, ep, splits, kps, st);
+      case T128x128x2w4: return run_mfma_tile<128, 128, 2, 2, 1, 2, 2, EPI, T, Ta>(g, ep, splits, kps, st);
+      default: break;
+    }
+  } else {
     switch (shape) {
       case T64x64g2: return run_mfma_tile<64, 64, 2, 2, 2, 4, 1, EPI, T, Ta>(g, ep, splits, kps, st);
       case T32x64g4: return run_mfma_tile<32, 64, 1, 2, 4, 3, 1, EPI, T, Ta>(g, ep, splits, kps, st);
@@ -731,7 +734,7 @@ static long tile_count(int s, int M, int N) {
 static int pick_shape(int M, int N, bool whole_heads) {
   for (int s : {T32x32g8, T32x64g4, T64x64g2, T64x128, T128x128})
     if (!(s == T32x32g8 && whole_heads) && tile_count(s, M, N) <= 256) return s;
-  return tile_count(T128x128, M, N) <= 1024 ? T128x128x2 : T128x128x2w4;
+  return T128x128x2;
 }
 
 #ifdef SR_GEMM_FORCE_SHAPE
@@ -755,16 +758,22 @@ struct DwPlan {
 };
 static DwPlan dw_plan(int M, int N, int K) {
   DwPlan p;
-  // Measured on MI355X (us, reduction included): up to some 8000 tokens 64 x 128 tiles while they fit one
-  // round (1024 x 1024 over 4050 tokens 23.2, 128 x 128 in four runs 28.7; 2048 x 1024 over 1024 13.8, 17.6),
-  // then 128 x 128.  Over more tokens the larger tile's fewer operand bytes outweigh its partial planes:
-  // over 16384, 2048 x 1024 121 -> 94 in two runs of 128 x 128, 1024 x 1024 66 -> 55 in four; from 192 tiles
-  // two workgroups per CU in two runs, 4096 x 1024 166 -> 155, 3072 x 1024 152 -> 136 (over 4050 tokens one
-  // run at one per CU stays ahead, 46.6 against 52.8).
+  // 64 x 128 tiles while they fit one round, then 128 x 128 (us, reduction included: 1024 x 1024 over 4050
+  // tokens 23.2, 128 x 128 in four runs 28.7; 2048 x 1024 over 1024 13.8, 17.6).
+  // Over 8192 tokens and more, what 64 x 128 tiles would cover in one run or two goes to 128 x 128 tiles in as many
+  // runs as fill the round: the larger tile's fewer operand bytes outweigh its partial planes.  In the step (us, two
+  // alternated medians of 13): generative block with 2 x 8192 conditioning tokens of 1024, whose K / V weights are
+  // 2048 x 1024, 1644 -> 1618, of 768 1282 -> 1258; adaLN 2 x 4096 x 1024 equal.  From 192 tiles, which one run
+  // fills, cutting only adds planes in the other stream's way (adaLN 2 x 4096 x 1024 3148 -> 3225, 8 x 1024 x
+  // 1024 2205 -> 2249), although alone it is ahead (4096 x 1024 over 16384 tokens 166 -> 155).
+  // Four waves past 2048 tokens: steps of adaLN blocks of 2 x 2048 x 1024, 1536 and 2048 1406, 2714 and 3903
+  // against 1433, 2754 and 3990 with eight, generative 1627 against 1653; at 1024 tokens eight are ahead (5.625 deg
+  // step 1834, with four 1892) and at 2048 the two are even (eight 851, four 838 at width 1024; 647, 665 at 768).
   const long t = tile_count(T128x128, M, N);
-  const int one = K > 2048 ? T128x128w4 : T128x128;
-  if (K >= 8192 && t >= 32) p.shape = t >= 192 ? T128x128x2w4 : one;
-  else if (t >= 192) p.shape = t >= 384 ? (K > 2048 ? T128x128x2w4 : T128x128x2) : one;
+  const bool many = K > 2048;
+  const int one = many ? T128x128w4 : T128x128;
+  if (t >= 384) p.shape = many ? T128x128x2w4 : T128x128x2;
+  else if (t >= 192 || (t >= 32 && K >= 8192)) p.shape = one;
   else p.shape = tile_count(T64x128, M, N) <= 256 ? T64x128 : one;
 #ifdef SR_GEMM_FORCE_SHAPE
   if (g_force_shape >= 0) p.shape = g_force_shape;
