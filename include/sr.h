@@ -357,8 +357,9 @@ SR_API sr_status sr_select_topk_scores(const sr_config* cfg, int32_t K, const fl
  * xattn_bwd, gather,
  * scatter_delta, gather_f32, scatter_f32, ln_fwd, ln_bwd,
  * gemm_<op> (qkv, o, fc1, fc2, dx_fc2, dx_fc1, dx_o, dx_qkv, dw_<op>), attn_fwd,
- * attn_bwd_dkv, attn_bwd_dq, attn_bwd_delta, reduce, colsum, convert, mod.  Where few workgroups
- * make dK/dV and dQ one launch (bf16, head dim 64), attn_bwd_dkv holds both passes. */
+ * attn_bwd_dkv, attn_bwd_dq, attn_bwd_f32 (both passes of fp32 storage), attn_bwd_delta, reduce,
+ * colsum, convert, mod.  Where few workgroups make dK/dV and dQ one launch (bf16, head dim 64),
+ * attn_bwd_dkv holds both passes. */
 SR_API sr_status sr_profile_start(const char* name_filter);
 SR_API sr_status sr_profile_stop(char* out, size_t out_bytes, size_t* needed);
 

@@ -2234,7 +2234,7 @@ hipError_t launch_attn_bwd(int dtype, const void* qkv, const void* dO, const flo
     };
     return D / H == 128 ? run(IC<128>{}) : D / H == 32 ? run(IC<32>{}) : run(IC<64>{});
   }
-  ProfScope ps("attn_bwd_generic", 8.0 * B * (double)S * S * D, 0, st);
+  ProfScope ps("attn_bwd_f32", 8.0 * B * (double)S * S * D, 0, st);
   const float* q = (const float*)qkv;
   const uint32_t all = (uint32_t)((size_t)B * S * 3 * D);
   return launch_attn_bwd_f32(q, 3 * D, all, q + D, 3 * D, all - D, (const float*)dO, lse, delta, (float*)dqkv, 3 * D,

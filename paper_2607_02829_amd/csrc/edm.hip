@@ -226,7 +226,7 @@ hipError_t edm_fwd(const EdmDims& d, const sr_edm_block_params* p, const void* e
   const int M = d.M, Mc = d.Mc, D = d.D, F = d.F, S = d.S, B = d.B;
   {
     ProfScope ps("convert", 0, (double)M * D * (d.elt + 4), st);
-    SR_TRY(launch_convert(d.dtype, h_in, kF32, sv[0].hin, (size_t)M * D, nullptr, 0, S, D, nullptr, st));
+    SR_TRY(launch_convert(d.dtype, h_in, kF32, sv[0].hin, (size_t)M * D, nullptr, st));
   }
   for (int i = 0; i < d.nb; ++i) {
     const EdmSaved& s = sv[(size_t)i];
@@ -369,7 +369,7 @@ hipError_t edm_bwd(const EdmDims& d, const sr_edm_block_params* p, const void* e
   }
   {   // g_res = fp32(dh_out) and its storage copy
     ProfScope ps("convert", 0, (double)M * D * (2 * d.elt + 4), st);
-    SR_TRY(launch_convert(d.dtype, dh_out, d.dtype, sc.g_act, (size_t)M * D, nullptr, 0, S, D, sc.g_res, st));
+    SR_TRY(launch_convert(d.dtype, dh_out, d.dtype, sc.g_act, (size_t)M * D, sc.g_res, st));
   }
   for (int i = d.nb - 1; i >= 0; --i) {
     const EdmSaved& s = sv[(size_t)i];
@@ -491,7 +491,7 @@ hipError_t edm_bwd(const EdmDims& d, const sr_edm_block_params* p, const void* e
   }
   {
     ProfScope ps("convert", 0, (double)M * D * (d.elt + 4), st);
-    SR_TRY(launch_convert(kF32, sc.g_res, d.dtype, dh_in, (size_t)M * D, nullptr, 0, S, D, nullptr, st));
+    SR_TRY(launch_convert(kF32, sc.g_res, d.dtype, dh_in, (size_t)M * D, nullptr, st));
   }
   for (int k = 0; k < kSlots; ++k) SR_TRY(join(k));   // every gradient is complete when st is
   return hipSuccess;

@@ -26,7 +26,7 @@
 //   EPI_DGELU     out_act = Ta(v * GELU'(z_in))                     (FC2 dX)
 //   EPI_ACT       out_act = Ta(v)                                   (O-proj dX)
 //   EPI_F32       out_f32[split] = v                                (dX for LN, dW partials)
-//   EPI_F32_ACC   out_f32 += v                                      (dcond over blocks)
+//   EPI_F32_ACC   out_f32 += v                                      (conditioning tokens' dX over blocks)
 //   EPI_DO        out_act = Ta(v); delta = per-head row sums of Ta(v) * O (attention backward)
 //   EPI_DW        dW = v, db = row sums of A (weight and bias gradients); with split-K each
 //                 split writes a partial plane and reduce_splits_kernel sums the planes in
@@ -41,7 +41,6 @@ namespace sr {
 struct EpiIn {
   f32x4 resid;
   i32x2 z;     // four activation-type values (bf16) of the GELU pre-activation
-  f32x4 zf;    // the same for fp32 activations (unused in the MFMA path)
 };
 
 template <int EPI>
@@ -674,18 +673,13 @@ template <int BM, int BN, int WM, int WN, int KG, int NST, int OCC, int EPI, typ
 static hipError_t run_mfma_tile(const GemmDesc& g, const EpiArgs& ep, int splits, int kps, hipStream_t st) {
   const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
   const dim3 grid((unsigned)(tiles_m * tiles_n * splits));
-#define SR_GEMM_L(AK, BK)                                                                                        \
-  SR_LAUNCH((gemm_mfma_kernel<BM, BN, WM, WN, KG, NST, OCC, AK, BK, EPI, T, Ta>), grid, dim3(64 * WM * WN * KG), \
-            0, st, (const bf16_t*)g.A, (const bf16_t*)g.B, g.M, g.N, g.K, (int)g.lda, (int)g.ldb,                 \
-            (uint32_t)g.a_bytes, (uint32_t)g.b_bytes, kps, tiles_m, tiles_n, ep)
-  if constexpr (EPI == EPI_DW) {
-    SR_GEMM_L(false, false);
-  } else {
-    if (!g.a_kmajor) return hipErrorInvalidValue;   // only the weight gradients read A token-major
-    if (g.b_kmajor) SR_GEMM_L(true, true);
-    else SR_GEMM_L(true, false);
-  }
-#undef SR_GEMM_L
+  // operand layouts (k-major or not): the forward reads both k-major, dX = dY W the weight n-major, dW = dY^T X
+  // both token-major
+  constexpr bool AK = EPI != EPI_DW, BK = EPI == EPI_BIAS_ACT || EPI == EPI_RESID || EPI == EPI_GELU;
+  if (g.a_kmajor != AK || g.b_kmajor != BK) return hipErrorInvalidValue;
+  SR_LAUNCH((gemm_mfma_kernel<BM, BN, WM, WN, KG, NST, OCC, AK, BK, EPI, T, Ta>), grid, dim3(64 * WM * WN * KG), 0, st,
+            (const bf16_t*)g.A, (const bf16_t*)g.B, g.M, g.N, g.K, (int)g.lda, (int)g.ldb, (uint32_t)g.a_bytes,
+            (uint32_t)g.b_bytes, kps, tiles_m, tiles_n, ep);
   return hipGetLastError();
 }
 

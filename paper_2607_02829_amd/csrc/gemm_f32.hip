@@ -251,8 +251,8 @@ static hipError_t run_f32(const GemmDesc& g, const EpiArgs& ep, hipStream_t st) 
 }
 
 // The block's products: forward (both operands k-major), dX (weight n-major) and dW (both token-major)
-// on widths that are multiples of 64.  The adaLN and FiLM products over a handful of samples stay with
-// the generic kernel.
+// on widths that are multiples of 64, which is every product of the fp32 mode: those of the adaLN and FiLM
+// conditioning, over a handful of samples, are in gemv.hip.
 bool gemm_f32_takes(const GemmDesc& g, int epi) {
   if (g.dtype != kF32 || g.N % 64) return false;
   switch (epi) {

@@ -315,9 +315,8 @@ __global__ __launch_bounds__(256) void gate_bwd_kernel(const float* __restrict__
         red[0][lane] + red[1][lane] + red[2][lane] + red[3][lane];
 }
 
-// y = T(x) elementwise (storage -> fp32, fp32 -> storage, fp32 -> activation), with an
-// optional per-sample column weight (adaLN gates): y[b,s,c] = x * w[b*wstride + c].
-// Eight consecutive elements per thread (n and D multiples of 8, so the eight share a row).
+// y = T(x) elementwise (storage -> fp32, fp32 -> storage), with an optional fp32 copy.
+// Eight consecutive elements per thread (n a multiple of 8).
 template <typename T>
 SR_DEV void load8(const T* p, float (&v)[8]) {
   if constexpr (sizeof(T) == 4) {
@@ -348,20 +347,12 @@ SR_DEV void store8(T* p, const float (&v)[8]) {
 
 template <typename TI, typename TO>
 __global__ __launch_bounds__(256) void convert_kernel(const TI* __restrict__ x, TO* __restrict__ y, uint32_t n8,
-                                                      const float* __restrict__ w, int wstride, uint32_t S,
-                                                      uint32_t D, float* __restrict__ y32) {
+                                                      float* __restrict__ y32) {
   const uint32_t stride = gridDim.x * 256u;
   for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < n8; i += stride) {
     const size_t o = (size_t)i * 8;
     float v[8];
     load8<TI>(x + o, v);
-    if (w) {
-      const uint32_t row = (uint32_t)(o / D), c = (uint32_t)(o - (size_t)row * D);
-      float g[8];
-      load8<float>(w + (size_t)(row / S) * wstride + c, g);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] *= g[e];
-    }
     store8<TO>(y + o, v);
     if (y32) store8<float>(y32 + o, v);
   }
@@ -551,14 +542,12 @@ hipError_t launch_gate_bwd(int dtype, const float* X, const void* Y, const float
   return hipGetLastError();
 }
 
-hipError_t launch_convert(int ti, const void* x, int to, void* y, size_t n, const float* w, int wstride, int S,
-                          int D, float* y32, hipStream_t st) {
-  if (n % 8 != 0 || D % 8 != 0 || n / 8 > 0xFFFFFFFFull) return hipErrorInvalidValue;
+hipError_t launch_convert(int ti, const void* x, int to, void* y, size_t n, float* y32, hipStream_t st) {
+  if (n % 8 != 0 || n / 8 > 0xFFFFFFFFull) return hipErrorInvalidValue;
   const uint32_t n8 = (uint32_t)(n / 8);
   dim3 g((unsigned)std::min<size_t>((n8 + 255) / 256, 65536));
-#define SR_CONV(TI, TO)                                                                                  \
-  SR_LAUNCH((convert_kernel<TI, TO>), g, dim3(256), 0, st, (const TI*)x, (TO*)y, n8, w, wstride, \
-                     (uint32_t)S, (uint32_t)D, y32)
+#define SR_CONV(TI, TO) \
+  SR_LAUNCH((convert_kernel<TI, TO>), g, dim3(256), 0, st, (const TI*)x, (TO*)y, n8, y32)
   if (ti == kBF16) {
     if (to == kBF16) SR_CONV(bf16_t, bf16_t); else SR_CONV(bf16_t, float);
   } else {

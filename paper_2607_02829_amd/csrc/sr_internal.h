@@ -126,8 +126,7 @@ int colsum_chunks(int S);
 // act = T(X * gate_b) and the partial column sums of X * Y (rows of part: colsum_chunks(S) per sample)
 hipError_t launch_gate_bwd(int dtype, const float* X, const void* Y, const float* gate, int gstride, int B, int S,
                            int N, void* act, float* part, hipStream_t st);
-hipError_t launch_convert(int ti, const void* x, int to, void* y, size_t n, const float* w, int wstride, int S, int D,
-                          float* y32, hipStream_t st);
+hipError_t launch_convert(int ti, const void* x, int to, void* y, size_t n, float* y32, hipStream_t st);
 hipError_t launch_reduce_cols(const float* part, int R, int G, int sum_groups, int width, int half, float* out_lo,
                               float* out_hi, int out_stride, hipStream_t st, int accumulate = 0);
 // Matrix-vector products of the adaLN conditioning (few rows B, bandwidth-bound in the weight):

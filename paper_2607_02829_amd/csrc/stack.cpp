@@ -177,7 +177,7 @@ hipError_t stack_fwd(const Dims& d, const sr_block_params* p, const void* cond, 
   auto run = [&]() -> hipError_t {
     if (!rt) {   // the fp32 residual stream from h_in (routed calls gather it in the first LayerNorm)
       ProfScope ps("convert", 0, (double)M * D * (e + 4), st);
-      SR_TRY(launch_convert(d.dtype, h_in, kF32, sv[0].hin, (size_t)M * D, nullptr, 0, S, D, nullptr, st));
+      SR_TRY(launch_convert(d.dtype, h_in, kF32, sv[0].hin, (size_t)M * D, nullptr, st));
     }
     for (int i = 0; i < d.nb; ++i) {
       const BlockSaved& s = sv[i];
@@ -430,7 +430,7 @@ hipError_t stack_bwd(const Dims& d, const sr_block_params* p, const void* cond, 
       SR_TRY(launch_gather_rows_f32(d.dtype, d.B, d.L, S, D, rt->x, rt->idx, sc.g_res, sc.g_act[0], rt->shared, st));
     } else {
       ProfScope ps("convert", 0, (double)M * D * (2 * e + 4), st);
-      SR_TRY(launch_convert(d.dtype, dh_out, d.dtype, sc.g_act[0], (size_t)M * D, nullptr, 0, S, D, sc.g_res, st));
+      SR_TRY(launch_convert(d.dtype, dh_out, d.dtype, sc.g_act[0], (size_t)M * D, sc.g_res, st));
     }
     void* const g0 = sc.g_act[0];   // gradient copy of the FC2 stage (read by dW_fc2)
     void* const g1 = sc.g_act[1];   // ... of the output-projection stage (read by dW_o)
@@ -581,7 +581,7 @@ hipError_t stack_bwd(const Dims& d, const sr_block_params* p, const void* cond, 
       SR_TRY(launch_scatter_f32_delta(d.dtype, d.B, d.L, S, D, rt->x, sc.g_res, rt->idx, rt->shared, st));
     } else {
       ProfScope ps("convert", 0, (double)M * D * (e + 4), st);
-      SR_TRY(launch_convert(kF32, sc.g_res, d.dtype, dh_in, (size_t)M * D, nullptr, 0, S, D, nullptr, st));
+      SR_TRY(launch_convert(kF32, sc.g_res, d.dtype, dh_in, (size_t)M * D, nullptr, st));
     }
     if (ln1_pending && (ln1_pending->ln1_w || ln1_pending->ln1_b)) {
       ProfScope ps("reduce", 0, (double)d.B * nln * 2 * D * 4, st);
