@@ -23,8 +23,9 @@ def test_pair(B, S, D):
     h, params, cond, dh = host_inputs(w, 1, S=S)
     a = gpu_blocks(w, S, h, params, cond, dh)
     items = pairs(a, oracle_blocks(w, h, params, cond, dh))
-    # the affine gradients of LN1 cancel over a few rows under nearly uniform attention: left to longer tests
-    check_pairs([p for p in items if not p[0].endswith(("ln1_w", "ln1_b"))], "bf16", "[pair]")
+    # over a few dozen rows under nearly uniform attention the affine gradients of LN1 cancel (their sums over the rows
+    # are of the size of the terms' own bf16 rounding): left to the longer cases
+    check_pairs([p for p in items if B * S > 128 or not p[0].endswith(("ln1_w", "ln1_b"))], "bf16", "[pair]")
     b = gpu_blocks(w, S, h, params, cond, dh)
     assert np.array_equal(a["dh_in"], b["dh_in"])
     assert all(np.array_equal(x[k], y[k], equal_nan=True) for x, y in zip(a["grads"], b["grads"]) for k in x)

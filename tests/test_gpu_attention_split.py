@@ -27,3 +27,17 @@ def test_split_attention_block(B, S, D, H):
     b = gpu_blocks(w, S, h, params, cond, dh)
     assert np.array_equal(a["h_out"], b["h_out"]) and np.array_equal(a["dh_in"], b["dh_in"])
     assert all(np.array_equal(x[k], y[k], equal_nan=True) for x, y in zip(a["grads"], b["grads"]) for k in x)
+
+
+# The forward's planes lie in the buffers of h1, z and GELU(z), so the MLP width decides how many runs it may have:
+# one (uncut) at F = D, three at 2 D, four from 3 D; at F = 5 D / 4 and 11 D / 4 the plane that does not fit whole is
+# left out.  The backward has four runs throughout.
+@pytest.mark.parametrize("S,D,H", [(2050, 256, 4), (2100, 128, 4)])
+@pytest.mark.parametrize("quarters", [4, 5, 8, 11, 12])
+def test_split_by_mlp_width(S, D, H, quarters):
+    F = D * quarters // 4 // 64 * 64
+    print(f"[split] S={S} D={D} H={H} F={F}", flush=True)
+    w = inputs.small(name="split", B=1, Hg=1, Wg=S, D=D, H=H, F=F)
+    h, params, cond, dh = host_inputs(w, 1, S=S)
+    a = gpu_blocks(w, S, h, params, cond, dh)
+    check_pairs(pairs(a, oracle_blocks(w, h, params, cond, dh)), "bf16", "[split]")
