@@ -166,7 +166,7 @@ sr_status sr_workspace_bytes(const sr_config* cfg, int32_t S, size_t* saved_byte
   SR_CHECK(S >= 1, SR_EINVAL, "S=%d must be >= 1", S);
   sr::Dims d = dims_of(cfg, S);
   if (saved_bytes) *saved_bytes = sr::layout_saved(d, nullptr, nullptr);
-  if (scratch_bytes) *scratch_bytes = sr::layout_scratch(d, nullptr, nullptr);
+  if (scratch_bytes) *scratch_bytes = sr::scratch_bytes(d);
   return SR_OK;
 }
 

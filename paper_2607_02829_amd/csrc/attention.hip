@@ -2076,14 +2076,9 @@ int attn_splits(int dtype, int B, int S, int H, int hd, int cap) {
   return (nt + per - 1) / per;   // no empty run
 }
 
-// n runs need n kRunTiles tiles in a sample and at most 1 / n of a round of workgroups in the call.
-size_t attn_split_rows(int dtype, int B, int S, int H, int hd) {
-  if (dtype != kBF16 || hd == 128) return 0;
-  size_t most = 0;
-  for (int n = 2; n <= kMaxSplit; ++n)
-    if ((S + KT - 1) / KT >= n * kRunTiles)
-      most = std::max(most, n * std::min((size_t)B * S, (size_t)split_rows(hd) * (split_workgroups(hd) / n / H)));
-  return most;
+size_t attn_run_rows(int dtype, int S, int H, int hd, int n) {
+  if (dtype != kBF16 || hd == 128 || (S + KT - 1) / KT < n * kRunTiles) return 0;
+  return (size_t)split_rows(hd) * (split_workgroups(hd) / n / H);
 }
 
 // The MFMA kernels on Sq query rows and Skv key/value rows (self-attention: both S, q, k and v

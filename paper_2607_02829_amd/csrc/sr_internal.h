@@ -188,9 +188,9 @@ struct AttnPart {
   float* ml = nullptr;
 };
 int attn_splits(int dtype, int B, int S, int H, int hd, int cap);
-// The most rows, over all its runs together, of any call of up to B samples of up to S tokens that is cut: what
-// its planes take (at most 50 MB of fp32 qkv rows).
-size_t attn_split_rows(int dtype, int B, int S, int H, int hd);
+// The most rows (B*S) of any call with n or more runs and at most S tokens per sample; 0 if there is none: n runs
+// need n times the tiles of one in a sample and at most 1 / n of a round of workgroups in the call.
+size_t attn_run_rows(int dtype, int S, int H, int hd, int n);
 hipError_t launch_attn_fwd(int dtype, const void* qkv, void* O, float* lse, int B, int S, int H, int D,
                            hipStream_t st, int nsplit = 1, const AttnPart& part = {});
 hipError_t launch_attn_colsum(int dtype, const void* qkv, const float* lse, float* colsum, int B, int S, int H, int D,

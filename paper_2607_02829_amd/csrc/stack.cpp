@@ -106,7 +106,8 @@ size_t layout_saved(const Dims& d, char* base, BlockSaved* out) {
 enum { kWgQkv = 0, kWgO = 1, kWgFc1 = 2, kWgFc2 = 3 };
 static const int kWeightGradShapes[4][2] = {{0, 1}, {1, 1}, {2, 1}, {1, 2}};
 
-size_t layout_scratch(const Dims& d, char* base, Scratch* out) {
+// planes: with those of a cut attention backward, which come last
+size_t layout_scratch(const Dims& d, char* base, Scratch* out, bool planes) {
   Carver c(base);
   const size_t M = d.M, D = d.D, F = d.F, e = d.elt;
   Scratch s{};
@@ -139,14 +140,29 @@ size_t layout_scratch(const Dims& d, char* base, Scratch* out) {
   // recomputed operands of the weight-gradient GEMMs (written and read on the second stream)
   s.u_rc = c.take<void>(M * D * e);
   s.gz_rc = c.take<void>(M * F * e);
-  // Planes of a cut attention backward.  How many runs a call has does not grow with its tokens, so their room
-  // is that of the call with the most rows in runs up to this size: a scratch buffer serves every smaller call.
   s.attn_splits = attn_splits(d.dtype, d.B, d.S, d.H, d.D / d.H, kMaxSplit);
-  float* planes = c.take<float>(attn_split_rows(d.dtype, d.B, d.S, d.H, d.D / d.H) * 3 * D * 4);
-  if (s.attn_splits > 1 && planes)
-    for (int k = 0; k < s.attn_splits; ++k) s.attn.p[k] = planes + k * M * 3 * D;
+  if (planes && s.attn_splits > 1)
+    for (int k = 0; k < s.attn_splits; ++k) s.attn.p[k] = c.take<float>(M * 3 * D * 4);
   if (out) *out = s;
   return c.off;
+}
+
+// A cut attention backward has planes that a call of more tokens or samples, with fewer runs or none, does not have.
+// So that a buffer sized for the larger call serves it, the size is the largest need of any call of up to B samples
+// of up to S tokens: the call's own, or for n runs that of the most rows that are cut so.  (64 tokens more per sample for the partial sums by chunks of up to 64 rows, of which more, shorter
+// samples of as many rows have one more each.)
+size_t scratch_bytes(const Dims& d) {
+  size_t most = layout_scratch(d, nullptr, nullptr);
+  for (int n = 2; n <= kMaxSplit; ++n) {
+    const size_t rows = attn_run_rows(d.dtype, d.S, d.H, d.D / d.H, n);
+    if (rows == 0) continue;
+    Dims e = d;
+    e.S = (int)std::min<size_t>(d.S, (rows + d.B - 1) / d.B + 64);
+    e.M = d.B * e.S;
+    const size_t plane = (std::min<size_t>(d.M, rows) * 3 * d.D * 4 + 255) & ~(size_t)255;
+    most = std::max(most, ((layout_scratch(e, nullptr, nullptr, false) + 255) & ~(size_t)255) + n * plane);
+  }
+  return most;
 }
 
 // Planes of a split attention forward, in buffers of the block that are written only after it: h1, z

@@ -42,7 +42,9 @@ struct Route {
 
 // Carve `base` (may be null: sizes only).  Returns the bytes used.
 size_t layout_saved(const Dims& d, char* base, BlockSaved* out /* [nb] or null */);
-size_t layout_scratch(const Dims& d, char* base, Scratch* out /* or null */);
+size_t layout_scratch(const Dims& d, char* base, Scratch* out /* or null */, bool planes = true);
+// What a caller provides: enough for every call of up to d.B samples of up to d.S tokens.
+size_t scratch_bytes(const Dims& d);
 
 // With `rt`, h_in / h_out (forward) and dh_out / dh_in (backward) are unused.
 hipError_t stack_fwd(const Dims& d, const sr_block_params* p, const void* cond, const void* h_in, void* h_out,

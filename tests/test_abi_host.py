@@ -64,9 +64,11 @@ def test_workspace_sizes_never_fall(D, H):
                 got = query(cfg, S)
                 assert got[0] >= last[0] and got[1] >= last[1], (query.__name__, B, S, last, got)
                 last = got
-        for S in range(64, 4096, 31):
+        for S in (*range(64, 4096, 61), 1025, 2048, 2049):
             last = (0, 0)
-            for B in range(1, 17):
+            for B in (*range(1, 17), 21, 32, 33, 43, 64, 65, 85, 128, 129, 257):
+                if B * 4096 * 4 * D * 4 >= 2 ** 31:
+                    break
                 got = query(_cfg(B=B, L=4096, D=D, H=H, F=4 * D, n_blocks=1), S)
                 assert got[0] >= last[0] and got[1] >= last[1], (query.__name__, B, S, last, got)
                 last = got
