@@ -31,6 +31,12 @@
  *  - Storage dtype (sr_config.dtype): SR_F32 or SR_BF16.  Activations, weights,
  *    biases, LayerNorm parameters and the conditioning vector are stored in it;
  *    all accumulation is fp32; weight gradients and dcond are always fp32.
+ *  - Determinism: the same call on the same inputs gives the same bits, whatever runs beside it.
+ *    A sample's bits may depend on the batch it is in: how a sum is grouped (tiles that share
+ *    its range, runs of a cut attention) follows the rows B*S and the heads of the call, and
+ *    with it the rounding of the stored activations.  In bf16 they no longer do once one sample
+ *    fills the GPU by itself: ceil(S/64) * D/64 > 256, and H * ceil(S/256) > 128 at head dim 64
+ *    or H * ceil(S/128) > 256 at head dim 32 (D = 1024 with 16 heads: from S = 2049).
  *  - Non-finite values: a NaN or Inf in a sample's inputs (tokens, conditioning) or in the
  *    parameters gives non-finite values in that sample's outputs and gradients (attention mixes
  *    every token of a sample, so all of its routed rows may be affected; which elements is not

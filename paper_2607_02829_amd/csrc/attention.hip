@@ -45,7 +45,7 @@ constexpr int NSTG = 3;      // LDS stages
 // head dim 128 the accumulators of a 32-row unit take twice the registers, so four waves (128
 // rows) per workgroup, one per SIMD with the whole register file: the register-explicit kernels
 // attn_fwd_h128, attn_bwd_dkv_h128 and attn_bwd_dq_h128 (the templates below are instantiated at
-// head dim 64).
+// head dims 32 and 64).
 template <int HD>
 constexpr int attn_waves() { return HD == 64 ? 8 : 4; }
 // At head dim 32 the vector work of a score (the exponential, the split of P into three bf16 parts,
@@ -2060,7 +2060,8 @@ static inline float attn_sl2(int hd) { return 1.4426950408889634f / sqrtf((float
 // 4050 tokens, combination included: four heads of 64 (64 workgroups, four runs) forward 71 -> 33,
 // dK/dV 112 -> 46, dQ 81 -> 32, combination 9 us; four heads of 32 (128 workgroups, four runs) 59 ->
 // 32, 114 -> 55, 63 -> 33, 9 us.
-// At head dim 128 the register-explicit kernels stay uncut (their models have eight heads or more).
+// The register-explicit kernels of head dim 128 and the calls on two buffers have no cut form: few heads leave CUs
+// idle there (two heads of 128 at 4050 tokens: 64 workgroups).
 static int split_rows(int hd) { return 32 * (hd == 64 ? attn_waves<64>() : attn_waves<32>()); }
 static int split_workgroups(int hd) { return hd == 64 ? 256 : 512; }   // one round of them
 constexpr int kRunTiles = 8;
