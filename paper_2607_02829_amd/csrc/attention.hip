@@ -1963,8 +1963,9 @@ __global__ __launch_bounds__(64 * NW, 8 / NW) void attn_colsum_mfma(const bf16_t
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) kf[ks] = mykey < S ? ld8(kp + (size_t)mykey * ld + ks * 16 + 8 * h32) : zero8();
 
-  const __amdgpu_buffer_rsrc_t rq = sample_rsrc(qkv, (uint32_t)((size_t)gridDim.z * S * ld), b, S, (int)ld);
-  const __amdgpu_buffer_rsrc_t rl = sample_rsrc(lse, (uint32_t)((size_t)gridDim.z * H * S), b, H, S);
+  // whole tensors: rows past the sample stay rows of S, whose P is replaced by zero, and enter no product
+  const __amdgpu_buffer_rsrc_t rq = make_rsrc(qkv, (uint32_t)((size_t)gridDim.z * S * ld * 2));
+  const __amdgpu_buffer_rsrc_t rl = make_rsrc(lse, (uint32_t)((size_t)gridDim.z * H * S * 4));
   const uint32_t qbase = (uint32_t)(((size_t)b * S * ld + hh * HD) * 2);
   const uint32_t lbase = (uint32_t)(((size_t)b * H + hh) * S * 4);
   auto load = [&](int t, int s) {

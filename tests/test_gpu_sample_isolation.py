@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 from gpu_helpers import gpu_blocks, host_inputs
-from paper_2607_02829_amd import inputs
+from paper_2607_02829_amd import abi, device, inputs
 from test_gpu_cross_attention import _data, _gpu
 
 pytestmark = pytest.mark.gpu
@@ -52,3 +52,27 @@ def test_blocks(S, D, H, dtype, kind):
             assert np.array_equal(clean[n][b], got[n][b]), f"{n} of sample {b}"
     if clean["dcond"] is not None:
         assert np.array_equal(clean["dcond"][[0, 2]], got["dcond"][[0, 2]])
+
+
+@pytest.mark.parametrize("S,D,H,dtype", [(45, 128, 2, "bf16"), (300, 128, 2, "bf16"), (45, 128, 4, "bf16"), (45, 128, 1, "f32")])
+def test_column_sums(S, D, H, dtype):
+    import torch
+    print(f"[isolation] column sums S={S} D={D} H={H} {dtype}", flush=True)
+    w = inputs.small(name="iso", dtype=dtype, B=3, Hg=1, Wg=S, D=D, H=H, F=2 * D, n_blocks=1)
+    h, params, _, _ = host_inputs(w, 1, S=S)
+    cfg = device.config_for(w, n_blocks=1)
+    dp = device.DeviceParams(params, w.kind)
+
+    def sums(x):
+        saved, scratch = device.workspace(cfg, S)
+        xd = device.to_device(x)
+        out = torch.empty((3, H, S), dtype=torch.float32, device="cuda")
+        abi.sr_dense_blocks_fwd(cfg, dp.array, None, xd, torch.empty_like(xd), saved, scratch)
+        abi.sr_attention_colsums(cfg, S, saved, 0, out)
+        torch.cuda.synchronize()
+        return out.cpu().numpy()
+
+    bad = h.copy()
+    bad[1, 0] = _bad(dtype, "nan")
+    clean, got = sums(h), sums(bad)
+    assert np.isfinite(clean).all() and np.array_equal(clean[[0, 2]], got[[0, 2]])
