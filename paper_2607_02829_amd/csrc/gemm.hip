@@ -731,16 +731,9 @@ static int pick_shape(int M, int N, bool whole_heads) {
   return T128x128x2;
 }
 
-#ifdef SR_GEMM_FORCE_SHAPE
-int g_force_shape = -1;   // standalone benchmarks: >= 0 overrides the choice
-#endif
-
 template <int EPI, typename T, typename Ta>
 static hipError_t run_mfma(const GemmDesc& g, const EpiArgs& ep, hipStream_t st) {
-  int shape = pick_shape(g.M, g.N, EPI == EPI_DO);
-#ifdef SR_GEMM_FORCE_SHAPE
-  if (g_force_shape >= 0) shape = g_force_shape;
-#endif
+  const int shape = pick_shape(g.M, g.N, EPI == EPI_DO);
   return run_shape<EPI, T, Ta>(shape, g, ep, 1, g.K, st);
 }
 
@@ -769,9 +762,6 @@ static DwPlan dw_plan(int M, int N, int K) {
   if (t >= 384) p.shape = many ? T128x128x2w4 : T128x128x2;
   else if (t >= 192 || (t >= 32 && K >= 8192)) p.shape = one;
   else p.shape = tile_count(T64x128, M, N) <= 256 ? T64x128 : one;
-#ifdef SR_GEMM_FORCE_SHAPE
-  if (g_force_shape >= 0) p.shape = g_force_shape;
-#endif
   const ShapeInfo si = shape_info(p.shape);
   const int bm = si.bm, bn = si.bn;
   const long tiles = (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn);
