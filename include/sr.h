@@ -143,7 +143,10 @@ SR_API const char* sr_version(void);
 
 /* Bytes of the `saved` (activations kept from forward for backward) and
  * `scratch` buffers needed by the block calls at S tokens per sample.  Neither falls when S or B
- * grows, all else equal: buffers sized for the largest call serve the smaller ones. */
+ * grows, all else equal: buffers sized for the largest call serve the smaller ones.  (Part of
+ * `scratch` is room for the partial results of an attention backward with few heads, which is cut
+ * into runs.  A call asks only for the rest: without that room it runs uncut, slower and with its
+ * sums in another order.) */
 SR_API sr_status sr_workspace_bytes(const sr_config* cfg, int32_t S, size_t* saved_bytes,
                              size_t* scratch_bytes);
 

@@ -140,9 +140,10 @@ sr_status check_params(const sr_config* c, const sr_block_params* p, const void*
 
 sr_status check_ws(const sr_config* c, int S, const void* saved, size_t saved_bytes, const void* scratch,
                    size_t scratch_bytes, bool need_scratch) {
-  size_t sb = 0, cb = 0;
-  sr_status s = sr_workspace_bytes(c, S, &sb, &cb);
-  if (s != SR_OK) return s;
+  // what this call cannot do without: sr_workspace_bytes adds room for the planes of a cut attention backward, its own
+  // and that of smaller calls in the same buffer
+  const sr::Dims d = dims_of(c, S);
+  const size_t sb = sr::layout_saved(d, nullptr, nullptr), cb = sr::layout_scratch(d, nullptr, nullptr, false);
   SR_PTR(saved, "saved");
   SR_CHECK(saved_bytes >= sb, SR_EWORKSPACE, "saved buffer has %zu bytes, needs %zu", saved_bytes, sb);
   if (need_scratch) {
@@ -297,7 +298,8 @@ sr_status sr_sparse_blocks_bwd(const sr_config* cfg, int32_t S, const sr_block_p
   if ((s = check_ws(cfg, S, saved, saved_bytes, scratch, scratch_bytes, true)) != SR_OK) return s;
   sr::Dims d = dims_of(cfg, S);
   return hip_status(sr::stack_bwd(d, params, cond, (const char*)saved, dh_out, dh_in, grads,
-                                  cfg->kind == SR_BLOCK_ADALN ? dcond : nullptr, (char*)scratch, (hipStream_t)stream),
+                                  cfg->kind == SR_BLOCK_ADALN ? dcond : nullptr, (char*)scratch, scratch_bytes,
+                                  (hipStream_t)stream),
                     "blocks_bwd");
 }
 
@@ -338,8 +340,8 @@ sr_status sr_routed_blocks_bwd(const sr_config* cfg, int32_t K, const int32_t* i
   sr::Route rt;
   rt.idx = idx; rt.x = g; rt.shared = cfg->idx_shared;
   return hip_status(sr::stack_bwd(d, params, cond, (const char*)saved, nullptr, nullptr, grads,
-                                  cfg->kind == SR_BLOCK_ADALN ? dcond : nullptr, (char*)scratch, (hipStream_t)stream,
-                                  &rt),
+                                  cfg->kind == SR_BLOCK_ADALN ? dcond : nullptr, (char*)scratch, scratch_bytes,
+                                  (hipStream_t)stream, &rt),
                     "routed_blocks_bwd");
 }
 

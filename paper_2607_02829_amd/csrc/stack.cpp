@@ -140,8 +140,8 @@ size_t layout_scratch(const Dims& d, char* base, Scratch* out, bool planes) {
   // recomputed operands of the weight-gradient GEMMs (written and read on the second stream)
   s.u_rc = c.take<void>(M * D * e);
   s.gz_rc = c.take<void>(M * F * e);
-  s.attn_splits = attn_splits(d.dtype, d.B, d.S, d.H, d.D / d.H, kMaxSplit);
-  if (planes && s.attn_splits > 1)
+  s.attn_splits = planes ? attn_splits(d.dtype, d.B, d.S, d.H, d.D / d.H, kMaxSplit) : 1;
+  if (s.attn_splits > 1)
     for (int k = 0; k < s.attn_splits; ++k) s.attn.p[k] = c.take<float>(M * 3 * D * 4);
   if (out) *out = s;
   return c.off;
@@ -357,11 +357,11 @@ void give_events(BwdEvents* e) {
 
 hipError_t stack_bwd(const Dims& d, const sr_block_params* p, const void* cond, const char* saved,
                      const void* dh_out, void* dh_in, const sr_block_grads* gr, float* dcond, char* scratch,
-                     hipStream_t st, const Route* rt) {
+                     size_t scratch_size, hipStream_t st, const Route* rt) {
   BlockSaved* sv = new BlockSaved[d.nb];
   layout_saved(d, const_cast<char*>(saved), sv);
-  Scratch sc;
-  layout_scratch(d, scratch, &sc);
+  Scratch sc;   // a buffer without room for the planes: attention uncut
+  layout_scratch(d, scratch, &sc, scratch_size >= layout_scratch(d, nullptr, nullptr));
   const int M = d.M, D = d.D, F = d.F, S = d.S;
   const size_t e = d.elt;
   const bool ada = d.kind == SR_BLOCK_ADALN;

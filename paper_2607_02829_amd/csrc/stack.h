@@ -50,7 +50,7 @@ size_t scratch_bytes(const Dims& d);
 hipError_t stack_fwd(const Dims& d, const sr_block_params* p, const void* cond, const void* h_in, void* h_out,
                      char* saved, hipStream_t st, const Route* rt = nullptr);
 hipError_t stack_bwd(const Dims& d, const sr_block_params* p, const void* cond, const char* saved,
-                     const void* dh_out, void* dh_in, const sr_block_grads* g, float* dcond, char* scratch,
+                     const void* dh_out, void* dh_in, const sr_block_grads* g, float* dcond, char* scratch, size_t scratch_size,
                      hipStream_t st, const Route* rt = nullptr);
 
 }  // namespace sr
